@@ -45,7 +45,7 @@ struct sg_mesh_s {
     float* d_geo = nullptr;
     int32_t* d_vc_off = nullptr;   // vertex -> corner lists (internal faces), for the vertex gradient
     int32_t* d_vc = nullptr;
-    int32_t part_he[sg::kParts + 1] = {};
+    int32_t part_face[sg::kParts + 1] = {};
     int32_t has_flip = 0;
     size_t bytes = 0;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timed, spare;   // walk-kernel event pairs
@@ -67,7 +67,7 @@ struct sg_mesh_s {
     sg::DevMesh dev(int32_t hole_avoid = 0) const {
         sg::DevMesh d{d_face,  d_F,     d_X,     d_half, d_perm,     d_order,
                       n_faces, n_verts, has_flip, {},   d_twin, hole_avoid, reinterpret_cast<const float4*>(d_geo)};
-        for (int p = 0; p <= sg::kParts; ++p) d.part_he[p] = part_he[p];
+        for (int p = 0; p <= sg::kParts; ++p) d.part_face[p] = part_face[p];
         return d;
     }
 };
@@ -642,12 +642,12 @@ int pack_mesh(const float* X_host, int64_t n_verts, const int32_t* F_host, int64
         for (int64_t h = 0; h < nh; ++h) {
             const int64_t g = twin[h];
             const uint32_t flip = g >= 0 && F[h] == F[g] ? 1u : 0u;   // same start vertex: orientations disagree
-            out.face[h / 3].nb[h % 3] = g < 0 ? -1 : (int32_t)(((uint32_t)g << 1) | flip);
+            out.face[h / 3].nb[h % 3] = g < 0 ? -1 : he_of((int32_t)(g / 3), (int)(g % 3)) | (int32_t)(flip << kNbFlipShift);
         }
         out.has_flip = 0;
         for (const FaceRec& q : out.face)
             for (int k = 0; k < 3; ++k)
-                if (q.nb[k] >= 0 && (q.nb[k] & 1)) out.has_flip = 1;
+                if (q.nb[k] >= 0 && nb_flip(q.nb[k])) out.has_flip = 1;
         out.vbnd = std::move(vbnd);
         out.twin.assign(twin.begin(), twin.end());
         out.F = std::move(F);
@@ -788,7 +788,7 @@ int sg_mesh_create(const float* X_host, int64_t n_verts, const int32_t* F_host, 
     m->n_meshes = n_meshes;
     m->mean_edge = pm.mean_edge;
     m->has_flip = pm.has_flip;
-    for (int p = 0; p <= sg::kParts; ++p) m->part_he[p] = (int32_t)(3 * pm.part_start[p]);
+    for (int p = 0; p <= sg::kParts; ++p) m->part_face[p] = (int32_t)pm.part_start[p];
     std::vector<int32_t> order32(pm.order.begin(), pm.order.end());
     // corners of each vertex (3 f + k over internal faces), grouped by vertex
     std::vector<int32_t> vc_off((size_t)n_verts + 1, 0), vc((size_t)3 * n_faces);

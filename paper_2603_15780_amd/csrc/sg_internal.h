@@ -9,6 +9,7 @@
 // the direction is carried as a fixed-point angle to the entry edge, so the
 // angle-preserving transition is an integer add of a corner angle.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace sg {
@@ -20,16 +21,31 @@ constexpr uint32_t kHalfPiFx = 0x40000000u;
 constexpr double kFxPerRad = 4294967296.0 / 6.283185307179586476925286766559;
 constexpr float kRadPerFx = 1.4629180792671596e-09f;   // 2 pi / 2^32
 
+// A half-edge in one word: the face in the low 27 bits, the edge index above
+// them.  Shifting the word left by 5 gives the face record's byte offset with
+// the edge index dropped, and the edge index is tested by comparing the word:
+// with ids 3 f + k the walk divided by 3 in every crossing, 9 issue slots of
+// its 109.
+constexpr int kHeShift = 27;
+constexpr int kNbFlipShift = 29;   // in a link: the neighbour traverses the edge the same way
+constexpr int32_t kHeFace = (1 << kHeShift) - 1;
+#define SG_HE_FN __host__ __device__ inline __attribute__((always_inline))
+SG_HE_FN int32_t he_of(int32_t f, int k) { return f | (k << kHeShift); }
+SG_HE_FN int32_t he_face(int32_t h) { return h & kHeFace; }
+SG_HE_FN int he_k(int32_t h) { return (int)((uint32_t)h >> kHeShift); }
+SG_HE_FN int32_t nb_he(int32_t nx) { return nx & ~(1 << kNbFlipShift); }
+SG_HE_FN uint32_t nb_flip(int32_t nx) { return ((uint32_t)nx >> kNbFlipShift) & 1u; }
+
 // One record per face (32 bytes, one aligned sector).  Edge k runs from
 // vertex k to vertex k+1 of the face; corner k is the angle at vertex k.
 struct alignas(32) FaceRec {
     float l[3];       // edge lengths |x_{k+1} - x_k|
     uint32_t c0, c1;  // corner angles at vertices 0 and 1 (fixed point); corner 2 = pi - c0 - c1
-    int32_t nb[3];    // half-edge entered when crossing edge k: (id << 1) | flip, or -1 (boundary)
+    int32_t nb[3];    // half-edge entered when crossing edge k (he_of) | flip << kNbFlipShift, or -1 (boundary)
 };
 static_assert(sizeof(FaceRec) == 32, "record must be one 32-byte sector");
 
-// The chart of half-edge h = 3 f + k as the walk sees it, rebuilt from the
+// The chart of half-edge (f, k) as the walk sees it, rebuilt from the
 // face record: a ray entering face f through edge k needs its exit test and
 // its two onward links.
 struct HalfEdgeRec {
@@ -37,8 +53,8 @@ struct HalfEdgeRec {
     float lac, lbc;   // lengths |ac| and |bc|
     float lab;        // length |ab| of the entry edge
     uint32_t A, B;    // corner angles at a and b (fixed point)
-    int32_t nca;      // half-edge entered when crossing edge c-a: (id << 1) | flip, or -1 (boundary)
-    int32_t nbc;      // half-edge entered when crossing edge b-c, same encoding
+    int32_t nca;      // link across edge c-a (FaceRec::nb), or -1 (boundary)
+    int32_t nbc;      // link across edge b-c, same encoding
 };
 
 // Faces are stored in a spatial (bisection) order cut into kParts contiguous
@@ -57,7 +73,7 @@ struct DevMesh {
     int64_t n_faces;
     int64_t n_verts;
     int32_t has_flip;           // some adjacent faces disagree in orientation (non-orientable or mixed)
-    int32_t part_he[kParts + 1];// half-edge id ranges of the parts
+    int32_t part_face[kParts + 1]; // face ranges of the parts
     const int32_t* twin;        // [3 n_faces] half-edge on the other side of each edge, -1 on the boundary
     int32_t hole_avoid;         // per call: 1 = trace along boundaries instead of stopping (Sec. 4)
     const float4* geo;          // [n_faces, 4]: the face's three vertex positions (w: its FaceRec's edge

@@ -2,7 +2,7 @@
 //
 // One ray per lane (Alg. gpu_parallel).  A ray is held in the chart of the
 // half-edge it entered through (see sg_internal.h):
-//   h        current half-edge record (face f = h / 3, entry edge k = h % 3)
+//   h        current half-edge (face f and entry edge k in one word, he_of)
 //   s, t     distance of the entry point from the edge's start a and end b
 //   phi      direction angle to the entry edge, fixed point, in [0, pi]
 //   Lhi+Llo  remaining length, compensated sum
@@ -110,26 +110,27 @@ SG_HD __forceinline__ HalfEdgeRec rec_decode(const FaceRec q, uint32_t k) {
     return r;
 }
 
-// The walk's gather: one 32-byte record with a 32-bit byte offset (f < 2^27).
+// The walk's gather: one 32-byte record with a 32-bit byte offset (f < 2^27;
+// shifting the half-edge word left by 5 drops the edge index above the face).
+SG_HD __forceinline__ const FaceRec& face_rec(const DevMesh& M, int32_t h) {
+    return *reinterpret_cast<const FaceRec*>(reinterpret_cast<const char*>(M.face) + ((uint32_t)h << 5));
+}
 SG_HD __forceinline__ HalfEdgeRec rec_at(const DevMesh& M, int32_t h) {
-    const uint32_t f = (uint32_t)h / 3u;
-    const FaceRec q = *reinterpret_cast<const FaceRec*>(reinterpret_cast<const char*>(M.face) + (f << 5));
-    return rec_decode(q, (uint32_t)h - 3u * f);
+    return rec_decode(face_rec(M, h), (uint32_t)he_k(h));
 }
 
 // The same chart from the 64-byte geometry record, which holds the walk
 // record's lengths and corners (start and end frames read that record anyway;
 // no caller of this form uses the neighbour links, which it leaves at -1).
 SG_HD __forceinline__ HalfEdgeRec rec_geo(const DevMesh& M, int32_t h) {
-    const uint32_t f = (uint32_t)h / 3u;
-    const float4* g = M.geo + 4 * (int64_t)f;
+    const float4* g = M.geo + 4 * (int64_t)he_face(h);
     const float4 g0 = g[0], g1 = g[1], g2 = g[2], g3 = g[3];
     FaceRec q;
     q.l[0] = g0.w; q.l[1] = g1.w; q.l[2] = g2.w;
     q.c0 = __builtin_bit_cast(uint32_t, g3.x);
     q.c1 = __builtin_bit_cast(uint32_t, g3.y);
     q.nb[0] = q.nb[1] = q.nb[2] = -1;
-    return rec_decode(q, (uint32_t)h - 3u * f);
+    return rec_decode(q, (uint32_t)he_k(h));
 }
 
 // hardware reciprocal (about 1 ulp); the walk only needs local accuracy
@@ -189,7 +190,7 @@ SG_HD __forceinline__ uint32_t rad_to_fx(float a) {
 template <bool kGeo = true>
 SG_HD int enter_face(const DevMesh& M, int32_t f, int k0, float ell0, float bA, float bB, float bC, uint32_t phi0,
                      float Lhi, float Llo, Ray& st) {
-    const int32_t h0 = 3 * f + k0;
+    const int32_t h0 = he_of(f, k0);
     const HalfEdgeRec r0 = kGeo ? rec_geo(M, h0) : rec_at(M, h0);
     float dy, dx;
     sincos_full(phi0, dy, dx);
@@ -235,7 +236,7 @@ SG_HD int enter_face(const DevMesh& M, int32_t f, int k0, float ell0, float bA, 
         phi = phi >= kPiFx + kHalfPiFx ? 0u : kPiFx;
     }
     st.phi = phi;
-    st.h = 3 * f + (k0 + k) % 3;
+    st.h = he_of(f, (k0 + k) % 3);
     // remaining length (Lhi + tau) + Llo, compensated (TwoSum)
     const float sum = Lhi + tau;
     const float bv = sum - Lhi;
@@ -445,8 +446,8 @@ SG_HD int ray_init(const DevMesh& M, int32_t fu, const float* bp, const float* v
 // Starts a walk at chart point (ex, ey) of half-edge h (an end point of an
 // earlier walk), direction phi to that chart's x-axis, length Lhi + Llo.
 SG_HD int enter_chart(const DevMesh& M, int32_t h, float ex, float ey, uint32_t phi, float Lhi, float Llo, Ray& st) {
-    const int32_t f = h / 3;
-    const int k0 = h - 3 * f;
+    const int32_t f = he_face(h);
+    const int k0 = he_k(h);
     const HalfEdgeRec r = rec_at(M, h);
     const float ell = r.lab;   // |ab| of this chart
     float bc = ey / r.cy;
@@ -466,18 +467,18 @@ enum VertexResult { kVertexDone = 0, kVertexNoSnap = 1, kVertexBoundary = 2 };
 // chart (else x0 is a for a c-a exit, b for a b-c exit).
 SG_HD __forceinline__ int vertex_rule(const DevMesh& M, Ray& st, const HalfEdgeRec& r, bool via_ca,
                                          bool at_apex, int32_t& x0_out) {
-    const int32_t f = st.h / 3, k = st.h - 3 * (st.h / 3);
+    const int32_t f = he_face(st.h), k = he_k(st.h);
     int xl, hv, roleA;
     int64_t acc;
     float ell;
     if (at_apex) {
         xl = (k + 2) % 3;
         if (via_ca) {   // walk from -d towards c->a; virtual entry across b-c, x0 is that chart's b
-            hv = 3 * f + (k + 1) % 3; roleA = 0;
+            hv = he_of(f, (k + 1) % 3); roleA = 0;
             acc = (int64_t)(int32_t)(st.phi + r.B - kPiFx);
             ell = r.lbc;
         } else {        // walk from -d towards c->b; virtual entry across c-a, x0 is that chart's a
-            hv = 3 * f + (k + 2) % 3; roleA = 1;
+            hv = he_of(f, (k + 2) % 3); roleA = 1;
             acc = (int64_t)(int32_t)(r.A - st.phi);
             ell = r.lac;
         }
@@ -513,8 +514,8 @@ SG_HD __forceinline__ int vertex_rule(const DevMesh& M, Ray& st, const HalfEdgeR
         const int32_t nx = roleA ? q.nca : q.nbc;
         ell = roleA ? q.lac : q.lbc;
         if (nx < 0) return kVertexBoundary;
-        hv = nx >> 1;
-        const uint32_t flip = (uint32_t)nx & 1u;
+        hv = nb_he(nx);
+        const uint32_t flip = nb_flip(nx);
         roleA ^= (int)flip;
         par ^= flip;
     }
@@ -576,7 +577,7 @@ SG_HD __forceinline__ void set_final(Final& fin, const Ray& st, float ex, float 
 // 3D frame of the chart of half-edge h: origin a, x-axis eu along a->b, ev
 // toward c, and the face normal (b - a) x (c - a), normalised.
 SG_HD __forceinline__ void chart_frame3(const DevMesh& M, int32_t h, float3& xa, float3& eu, float3& ev, float3& n) {
-    const int32_t f = h / 3, k = h - 3 * (h / 3);
+    const int32_t f = he_face(h), k = he_k(h);
     const int64_t f3 = 3 * (int64_t)f;
     xa = fvx(M, f3 / 3, k);
     const float3 xb = fvx(M, f3 / 3, (k + 1) % 3);
@@ -588,7 +589,7 @@ SG_HD __forceinline__ void chart_frame3(const DevMesh& M, int32_t h, float3& xa,
 }
 
 SG_HD __forceinline__ int32_t chart_vertex(const DevMesh& M, int32_t h, int which) {   // 0 a, 1 b, 2 c
-    const int32_t f = h / 3, k = h - 3 * (h / 3);
+    const int32_t f = he_face(h), k = he_k(h);
     return M.F[3 * (int64_t)f + (k + which) % 3];
 }
 
@@ -598,13 +599,13 @@ SG_HD __forceinline__ float3 proj_unit(float3 d, float3 n) { return nrm(sub(d, s
 // chart of f in which the direction's angle lies in [0, pi].
 SG_HD __forceinline__ void hole_final(const DevMesh& M, int32_t f, float3 P, float3 d, uint32_t par, int32_t ncross,
                                       uint64_t hash, int32_t status, Final& fin) {
-    int32_t hb = 3 * f;
+    int32_t hb = he_of(f, 0);
     float best = -2.f;
     float3 xa, eu, ev, n, bxa, beu, bev;
     for (int k = 0; k < 3; ++k) {
-        chart_frame3(M, 3 * f + k, xa, eu, ev, n);
+        chart_frame3(M, he_of(f, k), xa, eu, ev, n);
         const float dv = dot(d, ev);
-        if (dv > best) { best = dv; hb = 3 * f + k; bxa = xa; beu = eu; bev = ev; }
+        if (dv > best) { best = dv; hb = he_of(f, k); bxa = xa; beu = eu; bev = ev; }
     }
     chart_frame3(M, hb, xa, eu, ev, n);
     const float3 w = proj_unit(d, n);
@@ -623,7 +624,7 @@ SG_HD __forceinline__ void hole_final(const DevMesh& M, int32_t f, float3 P, flo
 // roleA, else b) point into the face's corner at x0?  Returns |d . n| (the
 // transport error) or -1, and the projection w.
 SG_HD __forceinline__ float corner_fit(const DevMesh& M, int32_t hv, int roleA, float3 d, float3& w) {
-    const int32_t f = hv / 3, k = hv - 3 * (hv / 3);
+    const int32_t f = he_face(hv), k = he_k(hv);
     const int64_t f3 = 3 * (int64_t)f;
     const int k0 = roleA ? k : (k + 1) % 3;   // x0's local index
     const float3 x0 = fvx(M, f3 / 3, k0);
@@ -653,7 +654,7 @@ SG_HD int hole_vertex_chain(const DevMesh& M, int32_t fc, int32_t x0, int32_t fr
                             Final& fin) {
     for (int guard = 0; guard < (1 << 20); ++guard) {
         // the fan of x0 between its two boundary edges: first to one end ...
-        int32_t hv = 3 * fc + (M.F[3 * (int64_t)fc] == x0 ? 0 : (M.F[3 * (int64_t)fc + 1] == x0 ? 1 : 2));
+        int32_t hv = he_of(fc, M.F[3 * (int64_t)fc] == x0 ? 0 : (M.F[3 * (int64_t)fc + 1] == x0 ? 1 : 2));
         int roleA = 1;
         uint32_t p = 0u;
         int g = 0;
@@ -661,16 +662,16 @@ SG_HD int hole_vertex_chain(const DevMesh& M, int32_t fc, int32_t x0, int32_t fr
             const HalfEdgeRec q = rec_at(M, hv);
             const int32_t nx = roleA ? q.nca : q.nbc;
             if (nx < 0) break;
-            hv = nx >> 1;
-            roleA ^= nx & 1;
-            p ^= (uint32_t)nx & 1u;
+            hv = nb_he(nx);
+            roleA ^= (int)nb_flip(nx);
+            p ^= nb_flip(nx);
         }
         const int32_t he0 = hv, y0 = chart_vertex(M, hv, 2);
         const uint32_t pe0 = p;
         // ... then back across the fan to the other end, testing each face
         {
-            const int32_t f = hv / 3, k = hv - 3 * (hv / 3);
-            hv = roleA ? 3 * f + (k + 2) % 3 : 3 * f + (k + 1) % 3;
+            const int32_t f = he_face(hv), k = he_k(hv);
+            hv = he_of(f, roleA ? (k + 2) % 3 : (k + 1) % 3);
             roleA ^= 1;
         }
         float best = 3.0e38f;
@@ -687,20 +688,20 @@ SG_HD int hole_vertex_chain(const DevMesh& M, int32_t fc, int32_t x0, int32_t fr
             const HalfEdgeRec q = rec_at(M, hv);
             const int32_t nx = roleA ? q.nca : q.nbc;
             if (nx < 0) { he1 = hv; y1 = chart_vertex(M, hv, 2); pe1 = p; break; }
-            hv = nx >> 1;
-            roleA ^= nx & 1;
-            p ^= (uint32_t)nx & 1u;
+            hv = nb_he(nx);
+            roleA ^= (int)nb_flip(nx);
+            p ^= nb_flip(nx);
         }
         const float3 X0 = ld3(M.X + 3 * (int64_t)x0);
         if (!first && ncross >= max_steps) {
             float3 xa, eu, ev, n;
-            chart_frame3(M, 3 * fc, xa, eu, ev, n);
+            chart_frame3(M, he_of(fc, 0), xa, eu, ev, n);
             hole_final(M, fc, X0, proj_unit(d, n), par, ncross, hash, kRayMaxSteps, fin);
             return kStepDone;
         }
         if (hb >= 0) {   // resume straight in that face, from x0 (its chart with a = x0)
-            const int32_t fb = hb / 3, kb = hb - 3 * (hb / 3);
-            const int32_t hr = rb ? hb : 3 * fb + (kb + 1) % 3;
+            const int32_t fb = he_face(hb), kb = he_k(hb);
+            const int32_t hr = rb ? hb : he_of(fb, (kb + 1) % 3);
             const HalfEdgeRec r = rec_at(M, hr);
             float3 xa, eu, ev, n;
             chart_frame3(M, hr, xa, eu, ev, n);
@@ -728,14 +729,14 @@ SG_HD int hole_vertex_chain(const DevMesh& M, int32_t fc, int32_t x0, int32_t fr
             const float c1 = dot(d, nrm(sub(ld3(M.X + 3 * (int64_t)y1), X0)));
             end = (c1 > c0 || (c1 == c0 && y1 < y0)) ? 1 : 0;
         }
-        const int32_t fe = (end ? he1 : he0) / 3;
+        const int32_t fe = he_face(end ? he1 : he0);
         const int32_t y = end ? y1 : y0;
         par ^= end ? pe1 : pe0;
         const float3 Y = ld3(M.X + 3 * (int64_t)y);
         const float3 e = sub(Y, X0);
         const float len = sqrtf(dot(e, e));
         float3 xa, eu, ev, n;
-        chart_frame3(M, 3 * fe, xa, eu, ev, n);
+        chart_frame3(M, he_of(fe, 0), xa, eu, ev, n);
         if (Lhi + Llo <= len) {   // the length ends on this boundary edge
             const float3 P = make_float3(fmaf(e.x, (Lhi + Llo) / len, X0.x), fmaf(e.y, (Lhi + Llo) / len, X0.y),
                                          fmaf(e.z, (Lhi + Llo) / len, X0.z));
@@ -764,7 +765,7 @@ SG_HD int hole_vertex_chain(const DevMesh& M, int32_t fc, int32_t x0, int32_t fr
 // non-apex end, with remaining length Lhi + Llo.  Slide along it.
 SG_HD int hole_edge(const DevMesh& M, const Ray& old, const HalfEdgeRec& r, bool via_ca, float mu, float omu,
                     float Lhi, float Llo, int32_t max_steps, Ray& st, Final& fin) {
-    const int32_t f = old.h / 3;
+    const int32_t f = he_face(old.h);
     // the exit point and the edge's two ends in the chart
     const float ax = via_ca ? 0.f : old.s + old.t;   // non-apex end (a or b)
     const float px = fmaf(mu, r.cx - ax, ax), py = mu * r.cy;
@@ -795,82 +796,122 @@ SG_HD int hole_edge(const DevMesh& M, const Ray& old, const HalfEdgeRec& r, bool
                              fnv_face(old.hash, (uint32_t)M.order[f]), false, max_steps, st, fin);
 }
 
-// One geodesic_step: find the exit of the current face (the smallest positive
-// barycentric exit parameter over the two non-entry edges), then cross the
-// edge into the next chart (transport_over_edge).  The crossing is computed
-// for every lane and committed with selects; stopping in the face, at the
-// step cap, at a vertex or on the boundary is one rarely taken branch.
-// kPre: the caller passes sin and cos of st.phi (psn, pcs), already computed.
-template <bool kHash, bool kFlip, bool kHole, bool kPre = false>
-SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps, float snap, Final& fin,
-                                   bool alive = true, float psn = 0.f, float pcs = 0.f) {
-    const HalfEdgeRec r = rec_at(M, st.h);
-    float sn, cs;
-    if constexpr (kPre) {
-        sn = psn;
-        cs = pcs;
-    } else {
-        sincos_fx(st.phi, sn, cs);
-    }
-    const float cross = fmaf(cs, r.cy, -sn * (r.cx - st.s));   // > 0: apex left of the ray
-    const bool via_ca = (cross + st.bias) < 0.f;
-    const float w = via_ca ? st.s : st.t;
+// Per-lane conditions as wave masks, which combine in scalar registers.  Left
+// as booleans, the selects of conditions in a step go through vector registers
+// and the conditions that the rare branch tests again are compared twice: 14
+// more issue slots per crossing.
+SG_HD __forceinline__ uint64_t lane_mask(bool c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ballot_w64(c);
+#else
+    return c ? ~0ull : 0ull;
+#endif
+}
+SG_HD __forceinline__ bool lane_of(uint64_t m) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+#else
+    return m != 0ull;
+#endif
+}
+
+// A face record's words.
+struct FaceWords {
+    float l0, l1, l2;
+    uint32_t c0, c1;
+    int32_t n0, n1, n2;
+};
+SG_HD __forceinline__ FaceWords face_words(const FaceRec& r) {
+    return FaceWords{r.l[0], r.l[1], r.l[2], r.c0, r.c1, r.nb[0], r.nb[1], r.nb[2]};
+}
+
+// The exit of a step: through edge c-a (via_ca) or b-c, lam along the ray, at
+// fraction mu of that edge from its non-apex end (omu: from the apex).
+struct Exit {
+    uint64_t mca, m0, m2;   // lanes that leave through c-a; whose entry edge is 0, is 2
+    uint32_t A, B;          // corners at a and b
+    float cx, cy;           // apex in the entry chart
+    float lam, mu, omu;
+};
+
+// The smallest positive barycentric exit parameter over the two non-entry
+// edges.  Only what this needs (the corners and |ca|, for the apex) is picked
+// from the record; the exit edge's length and link are picked later by that
+// edge's own index.
+SG_HD __forceinline__ void find_exit(const FaceWords& q, const Ray& st, float sn, float cs, Exit& x) {
+    // words as scalars first, so the picks by the entry edge stay selects on registers
+    const float l0 = q.l0, l1 = q.l1, l2 = q.l2;
+    const uint32_t c0 = q.c0, c1 = q.c1, c2 = kPiFx - (q.c0 + q.c1);
+    // the entry edge index, tested on the word itself (its top field)
+    const bool k0 = (uint32_t)st.h < (1u << kHeShift), k2 = (uint32_t)st.h >= (2u << kHeShift);
+    x.A = k0 ? c0 : (k2 ? c2 : c1);
+    x.B = k0 ? c1 : (k2 ? c0 : c2);
+    const float lac = k0 ? l2 : (k2 ? l1 : l0);
+    float sA, cA;
+    sincos_fx(x.A, sA, cA);
+    x.cx = lac * cA;
+    x.cy = lac * sA;
+    const float cross = fmaf(cs, x.cy, -sn * (x.cx - st.s));   // > 0: apex left of the ray
+    x.m0 = lane_mask(k0);
+    x.m2 = lane_mask(k2);
+    x.mca = lane_mask(cross < -st.bias);
+    const float w = lane_of(x.mca) ? st.s : st.t;
     const float acr = fabsf(cross);
     const float rD = rcp(fmaf(w, sn, acr));
-    const float lam = w * r.cy * rD;   // distance to the exit point
-    const float Lr = st.Lhi + st.Llo;
-    const float mu = w * sn * rD;      // exit point: fraction from the edge's non-apex end
-    const float omu = acr * rD;        // 1 - mu: fraction from the apex
-    const int32_t nx = via_ca ? r.nca : r.nbc;
-    // the next chart: the crossed edge keeps its points and angles
-    const float len = via_ca ? r.lac : r.lbc;
-    const float dm = mu * len, dom = omu * len;
-    float s2 = via_ca ? dm : dom;
-    float t2 = via_ca ? dom : dm;
-    uint32_t ph = via_ca ? st.phi - r.A : st.phi + r.B;
-    uint32_t par = st.par;
-    if (kFlip) {   // neighbour traverses the edge the same way: mirror the chart
-        const uint32_t flip = (uint32_t)nx & 1u;
-        const float tmp = s2;
-        s2 = flip ? t2 : s2;
-        t2 = flip ? tmp : t2;
-        ph = flip ? kPiFx - ph : ph;
-        par ^= flip;
-    }
-    const int32_t phs = (int32_t)ph;   // keep [0, pi] against rounding of grazing exits
-    ph = (uint32_t)(phs < 0 ? 0 : phs);
-    const float nh = st.Lhi - lam;                    // compensated remaining length
-    const float lo = st.Llo + ((st.Lhi - nh) - lam);
-    // (a lane slot without a ray steps a dummy state and never takes the rare branch)
-    const bool rare = alive && (!(lam < Lr) || (st.ncross >= max_steps) || (mu < snap) || (omu < snap) || (nx < 0));
-    // a lane that takes the rare branch keeps its state unchanged here, so the
-    // branch reads the step's starting state from st itself (no second copy
-    // of the state stays live across the update)
-    st.s = rare ? st.s : s2;
-    st.t = rare ? st.t : t2;
-    st.phi = rare ? st.phi : ph;
-    st.Lhi = rare ? st.Lhi : nh;
-    st.Llo = rare ? st.Llo : lo;
-    st.h = (rare || nx < 0) ? st.h : (nx >> 1);
-    st.par = rare ? st.par : par;
-    st.bias = rare ? st.bias : 0.f;
-    st.ncross += rare ? 0 : 1;
-    if (kHash && !rare) st.hash = fnv_face(st.hash, (uint32_t)M.order[st.h / 3]);
-    if (!rare) return kStepContinue;
+    x.lam = w * x.cy * rD;
+    x.mu = w * sn * rD;
+    x.omu = acr * rD;
+}
 
-    // ---- rare events, in priority order (st is the step's starting state)
-    if (!(lam < Lr)) {   // the ray ends inside this face (ties stay in the face)
-        set_final(fin, st, fmaf(Lr, cs, st.s), Lr * sn, kRayOk);
-        return kStepDone;
+// Crosses the exit edge into the next chart (transport_over_edge): the crossed
+// edge keeps its points and angles; the remaining length is compensated.
+template <bool kHash, bool kFlip>
+SG_HD __forceinline__ void cross_edge(const DevMesh& M, const Exit& x, float len, int32_t nx, Ray& st) {
+    const bool via_ca = lane_of(x.mca);
+    const float dm = x.mu * len, dom = x.omu * len;
+    uint32_t ph = st.phi + (via_ca ? 0u - x.A : x.B);
+    st.s = via_ca ? dm : dom;
+    st.t = via_ca ? dom : dm;
+    if (kFlip) {   // neighbour traverses the edge the same way: mirror the chart
+        const uint32_t flip = nb_flip(nx);
+        const float tmp = st.s;
+        st.s = flip ? st.t : st.s;
+        st.t = flip ? tmp : st.t;
+        ph = flip ? kPiFx - ph : ph;
+        st.par ^= flip;
     }
+    st.phi = (uint32_t)max((int32_t)ph, 0);   // keep [0, pi] against rounding of grazing exits
+    const float nh = st.Lhi - x.lam;
+    st.Llo = st.Llo + ((st.Lhi - nh) - x.lam);
+    st.Lhi = nh;
+    st.h = kFlip ? nb_he(nx) : nx;
+    st.bias = 0.f;
+    st.ncross += 1;
+    if (kHash) st.hash = fnv_face(st.hash, (uint32_t)M.order[he_face(st.h)]);
+}
+
+// A step that reaches the cap, a vertex or the boundary, from its start (the
+// exit is found again: these are a few in a million crossings).
+template <bool kHash, bool kFlip, bool kHole>
+SG_HD __forceinline__ int odd_step(const DevMesh& M, Ray& st, int32_t max_steps, float snap, Final& fin) {
+    const FaceRec rec = face_rec(M, st.h);
+    float sn, cs;
+    sincos_fx(st.phi, sn, cs);
+    Exit x;
+    find_exit(face_words(rec), st, sn, cs, x);
+    const HalfEdgeRec r = rec_decode(rec, (uint32_t)he_k(st.h));
+    const bool via_ca = lane_of(x.mca);
     if (st.ncross >= max_steps) {
         set_final(fin, st, st.s, 0.f, kRayMaxSteps);
         return kStepDone;
     }
-    if (mu < snap || omu < snap) {   // passing a vertex (transport_over_vertex)
+    const float nh = st.Lhi - x.lam;   // the remaining length past the vertex or the edge
+    const float lo = st.Llo + ((st.Lhi - nh) - x.lam);
+    const int32_t nx = via_ca ? r.nca : r.nbc;
+    if (x.mu < snap || x.omu < snap) {   // passing a vertex (transport_over_vertex)
         int32_t x0;
         Ray cand = st;
-        const bool at_apex = omu < snap;
+        const bool at_apex = x.omu < snap;
         const int vr = vertex_rule(M, cand, r, via_ca, at_apex, x0);
         if (vr == kVertexBoundary) {
             if constexpr (kHole) {   // the vertex lies lam along the ray, like a crossing
@@ -879,8 +920,8 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps
                 const float3 d = make_float3(fmaf(cs, eu.x, sn * ev.x), fmaf(cs, eu.y, sn * ev.y),
                                              fmaf(cs, eu.z, sn * ev.z));
                 const Ray o = st;
-                return hole_vertex_chain(M, o.h / 3, x0, -1, d, nh, lo, o.par, o.ncross, o.hash, true, max_steps, st,
-                                         fin);
+                return hole_vertex_chain(M, he_face(o.h), x0, -1, d, nh, lo, o.par, o.ncross, o.hash, true, max_steps,
+                                         st, fin);
             }
             set_final(fin, st, at_apex ? r.cx : (via_ca ? 0.f : st.s + st.t), at_apex ? r.cy : 0.f, kRayBoundary);
             return kStepDone;
@@ -889,7 +930,7 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps
             cand.Lhi = nh;
             cand.Llo = lo;
             cand.ncross = st.ncross + 1;
-            cand.hash = kHash ? fnv_face(st.hash, (uint32_t)M.order[cand.h / 3]) : 0ull;
+            cand.hash = kHash ? fnv_face(st.hash, (uint32_t)M.order[he_face(cand.h)]) : 0ull;
             st = cand;
             return kStepContinue;
         }
@@ -897,23 +938,64 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps
     if (nx < 0) {   // boundary edge: stop on it (Sec. 4, original behaviour), or slide along it
         if constexpr (kHole) {
             const Ray o = st;
-            return hole_edge(M, o, r, via_ca, mu, omu, nh, lo, max_steps, st, fin);
+            return hole_edge(M, o, r, via_ca, x.mu, x.omu, nh, lo, max_steps, st, fin);
         }
-        set_final(fin, st, fmaf(lam, cs, st.s), lam * sn, kRayBoundary);
+        set_final(fin, st, fmaf(x.lam, cs, st.s), x.lam * sn, kRayBoundary);
         return kStepDone;
     }
     // a vertex passed too far away to snap: an ordinary crossing
-    st.s = s2;
-    st.t = t2;
-    st.phi = ph;
-    st.Lhi = nh;
-    st.Llo = lo;
-    st.h = nx >> 1;
-    st.par = par;
-    st.bias = 0.f;
-    if (kHash) st.hash = fnv_face(st.hash, (uint32_t)M.order[st.h / 3]);
-    st.ncross = st.ncross + 1;
+    cross_edge<kHash, kFlip>(M, x, via_ca ? r.lac : r.lbc, nx, st);
     return kStepContinue;
+}
+
+// One geodesic_step: find the exit of the current face, then end in the face
+// or cross into the next chart; everything else is odd_step.  Each outcome
+// has its own branch and the odd one starts from the unchanged state, so every
+// state word is computed where it lives (merging the outcomes' values instead
+// took 7 to 14 register moves per crossing).
+// Bound by the L2's request rate where many rays are in flight (one 128-byte
+// line per crossing; a gather probe reaches 270 requests per ns over the 8
+// L2s, one per channel and cycle) and by the chain of a step where few are:
+// 109 -> 83 vector issue slots took 65,536 rays on 327,680 faces from 253 to
+// 237 us (the plain kernel), 1,048,576 from 1.101 to 1.091 ms, and the finite
+// differences of 1,048,576 queries, whose neighbouring lanes share lines, from
+// 2.83 to 2.77 ms.
+// Lanes that are not alive (a slot without a ray holds a dummy state) do
+// nothing.  kPre: the caller passes sin and cos of st.phi (psn, pcs).
+template <bool kHash, bool kFlip, bool kHole, bool kPre = false>
+SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps, float snap, Final& fin,
+                                   bool alive = true, float psn = 0.f, float pcs = 0.f) {
+    const FaceWords q = face_words(face_rec(M, st.h));
+    float sn, cs;
+    if constexpr (kPre) {
+        sn = psn;
+        cs = pcs;
+    } else {
+        sincos_fx(st.phi, sn, cs);
+    }
+    Exit x;
+    find_exit(q, st, sn, cs, x);
+    // the exit edge: entry + 2 (c-a) or entry + 1 (b-c), mod 3
+    const bool e0 = lane_of((x.mca & ~(x.m0 | x.m2)) | (~x.mca & x.m2)), e1 = lane_of((x.mca & x.m2) | (~x.mca & x.m0));
+    const float l0 = q.l0, l1 = q.l1, l2 = q.l2;
+    const int32_t n0 = q.n0, n1 = q.n1, n2 = q.n2;
+    const int32_t nx = e0 ? n0 : (e1 ? n1 : n2);
+    const float Lr = st.Lhi + st.Llo;
+    const uint64_t live = lane_mask(alive);
+    const uint64_t m_end = lane_mask(!(x.lam < Lr)) & live;   // ends inside this face (ties stay in the face)
+    const uint64_t m_odd = (lane_mask(st.ncross >= max_steps) | lane_mask(x.mu < snap) | lane_mask(x.omu < snap) |
+                            lane_mask(nx < 0)) & ~m_end & live;
+    if (lane_of(live & ~(m_end | m_odd)))
+        cross_edge<kHash, kFlip>(M, x, e0 ? l0 : (e1 ? l1 : l2), nx, st);
+    int ev = kStepContinue;
+    if (lane_of(m_end)) {
+        set_final(fin, st, fmaf(Lr, cs, st.s), Lr * sn, kRayOk);
+        ev = kStepDone;
+    }
+    if (__builtin_expect(m_odd != 0ull, 0)) {
+        if (lane_of(m_odd)) ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
+    }
+    return ev;
 }
 
 template <bool kHash, bool kFlip, bool kHole>
@@ -979,8 +1061,8 @@ SG_HD __forceinline__ void start_tangent_frame(const DevMesh& M, const ExpArgs& 
 // aux (nullable): the start-side terms saved at init, [L, (w . d0, w . q0) x K].
 SG_HD void write_final(const DevMesh& M, const ExpArgs& a, int64_t i, const Final& fin, float L,
                        const float* aux = nullptr) {
-    const int32_t fe = fin.h / 3;
-    const int ke = fin.h - 3 * fe;
+    const int32_t fe = he_face(fin.h);
+    const int ke = he_k(fin.h);
     const HalfEdgeRec r = rec_geo(M, fin.h);
     const int64_t f3 = 3 * (int64_t)fe;
     const float3 y0 = fvx(M, f3 / 3, 0);
@@ -1358,7 +1440,7 @@ SG_HD __forceinline__ GxRec gx_terms(const Ray& st, const float4& c, float sn, f
     const float Lr = st.Lhi + st.Llo;
     const float ru = fmaf(Lr, cs, st.s), rm = Lr * sn;
     GxRec r;
-    r.h = st.h;
+    r.h = 3 * he_face(st.h) + he_k(st.h);   // the sums' half-edge index
     r.q[0] = lm;
     r.q[1] = ln;
     r.q[2] = rm * ln;
@@ -1444,6 +1526,14 @@ SG_HD __forceinline__ QueueCursor queue_start(int nq) {
 
 SG_HD __forceinline__ int queue_range(int q, int nq) { return (q & 7) * (nq >> 3) + (q >> 3); }
 
+// Lane 0's value (the whole wave is active), in scalar registers: what follows
+// from it, the queue cursor and the loop bounds, then costs no vector issue.
+__device__ __forceinline__ unsigned long long wave_first(unsigned long long x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 // One claim of `want` consecutive slots by the whole wave (lane 0 does the
 // atomic).  Returns the first slot; slots at or past *hi belong to another
 // queue and are not this claim's.  When the claim reaches the end of its queue
@@ -1456,7 +1546,7 @@ __device__ __forceinline__ int64_t queue_claim(unsigned long long* ctr, const Qu
     hi = (int64_t)R.start[(j + 1) * R.stride] * R.per;
     unsigned long long b = 0ull;
     if (lane == 0) b = atomicAdd(ctr + (size_t)c.q * kQueueStride, (unsigned long long)want);
-    b = __shfl(b, 0);
+    b = wave_first(b);
     const int64_t first = lo + (int64_t)b;
     if (first + want >= hi) {   // on to the next range in XCD-major order
         const int jn = j + 1 == c.nq ? 0 : j + 1;
@@ -1482,7 +1572,7 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
     int64_t chunk = -1;
     int used = kGxChunk;
     bool spill = sink.rec == nullptr;
-    bool active = false;
+    uint64_t act = 0ull;   // lanes with a ray in flight
     QueueCursor qc = queue_start(nq);
     int64_t q = 0;
     int32_t ray = 0;   // with fin_out: the query index, carried in the initial state's crossing count
@@ -1491,13 +1581,14 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
     float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
     float gsn = 0.f, gcs = 0.f;   // with kGX: sin and cos of st.phi, shared by the crossing's terms and the next step
     for (;;) {
-        const uint64_t idle = __ballot(!active);
+        const uint64_t idle = ~act;
         const int nidle = __popcll(idle);
         if (nidle == 64 && qc.left == 0) break;
         if (qc.left > 0 && nidle >= refill_min) {
             int64_t hi = 0;
             const int64_t base = queue_claim(counter, R, lane, nidle, qc, hi);
-            if (!active) {
+            bool got = false;
+            if (!lane_of(act)) {
                 q = base + __popcll(idle & below);
                 if (q < hi) {
                     const StateRec rec = states[q];
@@ -1507,33 +1598,35 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
                             ray = rec.ncross;
                             st.ncross = 0;
                         }
-                        st.hash = kHash ? fnv_face(14695981039346656037ull, (uint32_t)M.order[rec.h / 3]) : 0ull;
+                        st.hash = kHash ? fnv_face(14695981039346656037ull, (uint32_t)M.order[he_face(rec.h)]) : 0ull;
                         if (kGX) {
                             c = cvec[q];
                             sincos_fx(st.phi, gsn, gcs);
                         }
-                        active = true;
+                        got = true;
                     }
                 }
             }
+            act |= lane_mask(got);
         }
         // walk until enough lanes are idle to refill (all of them once the queues are empty)
         const int stop_at = qc.left == 0 ? 64 : refill_min;
         for (;;) {
-            bool cross = false;
-            if (active) {
+            bool cross = false, done = false;
+            if (lane_of(act)) {
                 Final fin;
                 if (walk_step<kHash, kFlip, kHole, kGX>(M, st, max_steps, snap, fin, true, gsn, gcs) == kStepDone) {
                     if (fin_out) fin_out[ray] = fin;
                     else *reinterpret_cast<Final*>(&states[q]) = fin;
-                    active = false;
+                    done = true;
                 } else if constexpr (kGX) {
                     sincos_fx(st.phi, gsn, gcs);
                     cross = st.bias == 0.f;   // an edge crossing (a vertex passage leaves a bias)
                 }
             }
+            act &= ~lane_mask(done);
             if constexpr (kGX) {
-                const uint64_t m = __ballot(cross);
+                const uint64_t m = lane_mask(cross);
                 if (m) {
                     const int cw = __popcll(m);
                     if (!spill && used + cw > kGxChunk) {   // close this chunk, claim the block's next
@@ -1561,7 +1654,7 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
                     if (!spill) used += cw;
                 }
             }
-            if (__popcll(__ballot(!active)) >= stop_at) break;
+            if (64 - __popcll(act) >= stop_at) break;
         }
     }
     if (kGX && chunk >= 0 && lane == 0) sink.fill[chunk] = (uint32_t)used;
@@ -1597,7 +1690,7 @@ __device__ __forceinline__ void walk_loop2(const DevMesh& M, StateRec* states, Q
                     const StateRec rec = states[q0];
                     if (rec.h >= 0) {
                         unpack_state(rec, s0);
-                        s0.hash = kHash ? fnv_face(14695981039346656037ull, (uint32_t)M.order[rec.h / 3]) : 0ull;
+                        s0.hash = kHash ? fnv_face(14695981039346656037ull, (uint32_t)M.order[he_face(rec.h)]) : 0ull;
                         a0 = true;
                     }
                 }
@@ -1608,7 +1701,7 @@ __device__ __forceinline__ void walk_loop2(const DevMesh& M, StateRec* states, Q
                     const StateRec rec = states[q1];
                     if (rec.h >= 0) {
                         unpack_state(rec, s1);
-                        s1.hash = kHash ? fnv_face(14695981039346656037ull, (uint32_t)M.order[rec.h / 3]) : 0ull;
+                        s1.hash = kHash ? fnv_face(14695981039346656037ull, (uint32_t)M.order[he_face(rec.h)]) : 0ull;
                         a1 = true;
                     }
                 }
@@ -1915,7 +2008,7 @@ constexpr int kSlice = 2048;   // tags per claimed slice (also the per-wave list
 SG_HD __forceinline__ int part_of(const DevMesh& M, int32_t h) {
     int p = 0;
 #pragma unroll
-    for (int k = 1; k < kParts; ++k) p += h >= M.part_he[k] ? 1 : 0;
+    for (int k = 1; k < kParts; ++k) p += he_face(h) >= M.part_face[k] ? 1 : 0;
     return p;
 }
 
@@ -1972,7 +2065,7 @@ __global__ __launch_bounds__(256) void k_walk_round(DevMesh M, StateRec* states,
     int32_t* list = lists[threadIdx.x >> 6];
     const int home = (int)(blockIdx.x % kParts);
     const uint8_t want = (uint8_t)((round << 3) | home);
-    const int32_t lo = M.part_he[home], hi = M.part_he[home + 1];
+    const int32_t lo = M.part_face[home], hi = M.part_face[home + 1];
     bool active = false, exhausted = false;
     int list_n = 0, list_pos = 0;
     int32_t ray = 0;
@@ -2022,7 +2115,7 @@ __global__ __launch_bounds__(256) void k_walk_round(DevMesh M, StateRec* states,
                     *reinterpret_cast<Final*>(&states[ray]) = fin;
                     tags[ray] = kTagDone;
                     active = false;
-                } else if (restrict_part && (st.h < lo || st.h >= hi)) {
+                } else if (restrict_part && (he_face(st.h) < lo || he_face(st.h) >= hi)) {
                     states[ray] = pack_state(st);
                     if (kHash) hashes[ray] = st.hash;
                     tags[ray] = (uint8_t)(((round + 1) << 3) | part_of(M, st.h));
@@ -2059,8 +2152,8 @@ __global__ __launch_bounds__(256) void k_finish(DevMesh M, ExpArgs a, const Stat
 // finite differences of the geodesic scheme subtract nearby points, so they
 // are formed from small local vectors rather than from rounded 3D positions.
 SG_HD __forceinline__ float3 final_offset(const DevMesh& M, const Final& fin, float3 o, int32_t& fe_out) {
-    const int32_t fe = fin.h / 3;
-    const int ke = fin.h - 3 * fe;
+    const int32_t fe = he_face(fin.h);
+    const int ke = he_k(fin.h);
     const HalfEdgeRec r = rec_geo(M, fin.h);
     const int64_t f3 = 3 * (int64_t)fe;
     const float3 y0 = sub(fvx(M, f3 / 3, 0), o);
@@ -2076,8 +2169,8 @@ SG_HD __forceinline__ float3 final_offset(const DevMesh& M, const Final& fin, fl
 
 // Tangent and orientation-consistent normal at the end of a walk.
 SG_HD __forceinline__ void final_frame(const DevMesh& M, const Final& fin, float3& d3, float3& n3) {
-    const int32_t fe = fin.h / 3;
-    const int ke = fin.h - 3 * fe;
+    const int32_t fe = he_face(fin.h);
+    const int ke = he_k(fin.h);
     const int64_t f3 = 3 * (int64_t)fe;
     const float3 ya = fvx(M, f3 / 3, ke);
     const float3 yb = fvx(M, f3 / 3, (ke + 1) % 3);
@@ -2208,7 +2301,7 @@ SG_HD void bwd_stage1(const DevMesh& M, const BwdArgs& a, StateRec* s1, int per_
                                                                                                        : dead_state();
     sh[3 * i] = enter_face(M, S.f, 0, S.l0, S.b0, S.b1, S.b2, 0u, ep, 0.f, st) == kInitOk ? pack_state(st)
                                                                                           : dead_state();
-    const uint32_t Av = rec_geo(M, 3 * S.f).A;   // angle of e_v = unit(x2 - x0) in the chart
+    const uint32_t Av = rec_geo(M, he_of(S.f, 0)).A;   // angle of e_v = unit(x2 - x0) in the chart
     sh[3 * i + 1] = enter_face(M, S.f, 0, S.l0, S.b0, S.b1, S.b2, Av, ep, 0.f, st) == kInitOk ? pack_state(st)
                                                                                               : dead_state();
 }
@@ -2231,8 +2324,8 @@ SG_HD __forceinline__ Final saved_final(const DevMesh& M, const BwdArgs& a, int6
     const float b0 = a.b_out[3 * i], b1 = a.b_out[3 * i + 1], b2 = a.b_out[3 * i + 2];
     const float bs = b0 + b1 + b2;
     if (!(bs > 0.f) || !__builtin_isfinite(bs)) return F;
-    const HalfEdgeRec r = rec_geo(M, 3 * fe);
-    F.h = 3 * fe;
+    const HalfEdgeRec r = rec_geo(M, he_of(fe, 0));
+    F.h = he_of(fe, 0);
     F.ex = fmaf(b1 / bs, r.lab, (b2 / bs) * r.cx);
     F.ey = (b2 / bs) * r.cy;
     float Lo, Llo;
@@ -2274,7 +2367,7 @@ SG_HD void bwd_stage2(const DevMesh& M, const BwdArgs& a, StateRec* s1, int per_
                                                                                               : dead_state();
     if (!do_shift) return;
     const uint32_t psi_u = phi0;                              // v relative to e_u
-    const uint32_t psi_v = phi0 - rec_geo(M, 3 * S.f).A;       // v relative to e_v
+    const uint32_t psi_v = phi0 - rec_geo(M, he_of(S.f, 0)).A;       // v relative to e_v
     const uint32_t du = (Fu.flags & kParity) ? Fu.phi - psi_u : Fu.phi + psi_u;
     const uint32_t dv = (Fv.flags & kParity) ? Fv.phi - psi_v : Fv.phi + psi_v;
     out[0] = enter_chart(M, Fu.h, Fu.ex, Fu.ey, du, L, 0.f, st) == kInitOk ? pack_state(st) : dead_state();
@@ -2316,7 +2409,7 @@ SG_HD void gfd_assemble(const DevMesh& M, const BwdArgs& a, const StateRec* s1, 
         return;
     }
     float3 o, eu2, ev2;
-    face_uv(M, F0.h / 3, o, eu2, ev2);
+    face_uv(M, he_face(F0.h), o, eu2, ev2);
     int32_t ft;
     const float3 q0 = final_offset(M, F0, o, ft);
     const float iv = 1.0f / a.eps_v, ip = 1.0f / a.eps_p;
@@ -2326,7 +2419,7 @@ SG_HD void gfd_assemble(const DevMesh& M, const BwdArgs& a, const StateRec* s1, 
     const float3 cv = scl(sub(final_offset(M, Fv, o, ft), q0), ip);
     const float2 j0 = pinv_uv(eu2, ev2, cpar), j1 = pinv_uv(eu2, ev2, cperp);   // J^v columns
     const float2 k0 = pinv_uv(eu2, ev2, cu), k1 = pinv_uv(eu2, ev2, cv);         // J^p columns
-    const float3 g = load_g(M, a, i, F0.h / 3);
+    const float3 g = load_g(M, a, i, he_face(F0.h));
     const float h0 = dot(eu2, g), h1 = dot(ev2, g);
     // J^T (M'^T g)
     const float c0 = fmaf(j0.x, h0, j0.y * h1), c1 = fmaf(j1.x, h0, j1.y * h1);
@@ -2430,7 +2523,7 @@ SG_HD void ep_walked(const DevMesh& M, const BwdArgs& a, const StateRec* s1, int
     }
     float3 d3, n3;
     final_frame(M, F0, d3, n3);
-    ep_grad(M, a, i, S, phi0, d3, n3, F0.h / 3);
+    ep_grad(M, a, i, S, phi0, d3, n3, he_face(F0.h));
 }
 
 // ---------------------------------------------------------------- vertex-position gradient
@@ -2466,7 +2559,7 @@ SG_HD void gradx_init(const DevMesh& M, const BwdArgs& a, const StateRec* s1, in
         if (F0.h < 0 || ((F0.flags >> 8) & 0xffu) != (uint32_t)kRayOk) return;
         if (F0.flags & kBndBit) return;   // slid along a boundary: not a chain of hinges
         final_frame(M, F0, d3, n3);
-        fe = F0.h / 3;
+        fe = he_face(F0.h);
     } else {    // the end frame from the forward's saved outputs (faces agree in orientation, no slides)
         if (a.status_in[i] != kRayOk) return;
         const int32_t fo = a.f_out[i];

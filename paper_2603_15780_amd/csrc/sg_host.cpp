@@ -203,7 +203,9 @@ int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1
     return SG_OK;
 }
 
-sg::WalkSched sched(const sg_opts& o) { return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues}; }
+sg::WalkSched sched(const sg_opts& o, const sg_mesh_s* m) {
+    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1};
+}
 
 // Workspace of a call: the caller's (checked) or a stream-ordered allocation.
 struct Workspace {
@@ -915,7 +917,7 @@ int sg_exp_transport(sg_mesh mesh, int64_t n, const int32_t* f, const float* b, 
     }
     hipError_t e = part ? sg::launch_exp_partitioned(mesh->dev(o.boundary_mode), a, ws.p, o.walk_blocks, o.refill_min, st, ev.first,
                                                      ev.second)
-                        : sg::launch_exp_persistent(mesh->dev(o.boundary_mode), a, ws.p, sched(o), st, ev.first,
+                        : sg::launch_exp_persistent(mesh->dev(o.boundary_mode), a, ws.p, sched(o, mesh), st, ev.first,
                                                     ev.second);
     if (ev.first) mesh->timed.push_back(ev);
     const hipError_t e2 = give_workspace(ws, st);
@@ -952,7 +954,7 @@ int sg_exp_transport_noalloc(sg_mesh mesh, int64_t n, const int32_t* f, const fl
     void* ws = nullptr;
     hipError_t e = sg::noalloc_scratch(&ws);
     if (e != hipSuccess) return hip_fail(e, "scratch address");
-    e = sg::launch_exp_persistent(mesh->dev(o.boundary_mode), a, ws, sched(o), st, nullptr, nullptr);
+    e = sg::launch_exp_persistent(mesh->dev(o.boundary_mode), a, ws, sched(o, mesh), st, nullptr, nullptr);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
     return SG_OK;
 }
@@ -1009,7 +1011,7 @@ int sg_exp_backward_transport(sg_mesh mesh, int32_t mode, int64_t n, const int32
                                                b_out != nullptr, v_out != nullptr, status != nullptr),
                         st, ws);
     if (rc != SG_OK) return rc;
-    hipError_t e = sg::launch_backward(mesh->dev(o.boundary_mode), a, ws.p, sched(o), st);
+    hipError_t e = sg::launch_backward(mesh->dev(o.boundary_mode), a, ws.p, sched(o, mesh), st);
     const hipError_t e2 = give_workspace(ws, st);
     if (e != hipSuccess) return hip_fail(e, "backward launch");
     if (e2 != hipSuccess) return hip_fail(e2, "workspace release");

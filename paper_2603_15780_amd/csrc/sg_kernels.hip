@@ -1196,28 +1196,44 @@ constexpr int kQueueStride = 32;   // counters 256 bytes apart
 constexpr size_t kQueueBytes = (size_t)kMaxQueues * kQueueStride * sizeof(unsigned long long);
 
 // The walk order: queue range j (nq ranges of equal internal-face counts, in
-// the spatial bisection order), then length class c (longest first), then
-// spatial sub-bucket.  Taking the long rays of a range first keeps the last
+// the spatial bisection order), then direction class d (the largest component
+// of v and its sign), then length class c (longest first), then spatial
+// sub-bucket.  The rays that an XCD has in flight (24,576 of a range's) then
+// sweep one sector of the mesh instead of the whole disc around the range, so
+// more of what they touch stays in its 4 MB L2: 4,194,304 rays of length up to
+// pi on 1,310,720 faces 19.9 -> 17.1 ms, 1,048,576 on 327,680 faces 1.09 ->
+// 1.06 ms.  A handle of several meshes takes one direction class: its ranges
+// hold whole meshes, which fit the L2 by themselves (16 meshes, 1,400,003 rays:
+// 0.601 ms with one class, 0.633 with six); so does a batch of fewer than four
+// rays per lane, most of which is in flight at once whatever the order (200,003
+// rays on a mesh with holes: 0.942 ms with one class, 1.013 with six, whose last
+// sector's long rays start late).  Taking the long rays of a class first keeps the last
 // rays in flight short, so the waves drain quickly once the queues are empty.
 // Length classes are octaves of |v|^2 below the longest ray of the call, from
 // the difference of the float bit patterns (integer arithmetic, so every
 // kernel that recomputes a ray's bucket gets the same one).
 constexpr int kLenClasses = 8;
+constexpr int kDirClasses = 6;
 constexpr int kVmaxWord = kMaxBuckets + 1;   // cnt[kVmaxWord]: float bits of the longest |v|^2
 constexpr int kLenBlocks = 1024;             // k_len_max blocks; their partial maxima follow kVmaxWord
+static_assert(kMaxBuckets / (kMaxQueues * kDirClasses * kLenClasses) >= 1, "every range, direction and length class has a bucket");
 constexpr int kCountWords = kMaxBuckets + 2 + kLenBlocks;   // words of the bucket-count array
 
 struct RayOrder {
     int nq;    // queue ranges
-    int sub;   // spatial sub-buckets per (range, class)
-    int nb;    // nq * kLenClasses * sub + 1 buckets (the last: face id out of range)
+    int dirs;  // direction classes: kDirClasses or 1
+    int sub;   // spatial sub-buckets per (range, direction, length class)
+    int nb;    // nq * stride() + 1 buckets (the last: face id out of range)
+    SG_HD int stride() const { return dirs * kLenClasses * sub; }   // buckets per range
 };
 
-inline RayOrder ray_order(int nq) {
+inline RayOrder ray_order(const WalkSched& w, int64_t states) {
     RayOrder o;
+    const int nq = w.queues;
     o.nq = nq;
-    o.sub = kMaxBuckets / (nq * kLenClasses);
-    o.nb = nq * kLenClasses * o.sub + 1;
+    o.dirs = w.one_mesh && states >= 4 * 256 * (int64_t)w.blocks ? kDirClasses : 1;
+    o.sub = kMaxBuckets / (nq * o.dirs * kLenClasses);
+    o.nb = nq * o.stride() + 1;
     return o;
 }
 
@@ -1236,7 +1252,12 @@ SG_HD __forceinline__ int ray_bucket_int(const DevMesh& M, int32_t fi, const flo
         const uint32_t d = (vmax_bits - __float_as_uint(l2)) >> 23;
         c = d < (uint32_t)kLenClasses ? (int)d : kLenClasses - 1;
     }
-    return (int)((j * kLenClasses + c) * o.sub + sb);
+    int d = 0;
+    if (o.dirs > 1) {
+        const float ax = fabsf(v[0]), ay = fabsf(v[1]), az = fabsf(v[2]);
+        d = ax >= ay && ax >= az ? (v[0] < 0.f ? 1 : 0) : (ay >= az ? (v[1] < 0.f ? 3 : 2) : (v[2] < 0.f ? 5 : 4));
+    }
+    return (int)(((j * o.dirs + d) * kLenClasses + c) * o.sub + sb);
 }
 
 SG_HD __forceinline__ int ray_bucket(const DevMesh& M, int32_t fu, const float* v, const RayOrder& o, uint32_t vmax_bits) {
@@ -2880,12 +2901,12 @@ hipError_t launch_exp_persistent(const DevMesh& M, const ExpArgs& a, void* ws, c
     // so the epilogue streams them; the two-ray form leaves them in the slots
     const bool by_query = a.rays_per_lane != 2;
     auto* fin = by_query ? reinterpret_cast<Final*>(p + L.fin) : nullptr;
-    const RayOrder ord = ray_order(w.queues);
+    const RayOrder ord = ray_order(w, a.n);
     auto* fint = reinterpret_cast<int32_t*>(p + L.fint);
     order_rays(M, a.n, a.f, a.v, cnt, slot, ord, s, fint);
     hipLaunchKernelGGL(k_init, dim3((unsigned)grid), dim3(block), 0, s, M, a, states, counter, aux,
                        (const uint32_t*)cnt, slot, ord, fin, (const int32_t*)fint);
-    const QueueRanges R{cnt, kLenClasses * ord.sub, 1};
+    const QueueRanges R{cnt, ord.stride(), 1};
     if (ev0) (void)hipEventRecord(ev0, s);
     if (!by_query)
         SG_DISPATCH(k_walk2, (a.debug & 2u) != 0u, M.has_flip != 0, dim3((unsigned)w.blocks), dim3(block), s, M,
@@ -3109,7 +3130,7 @@ hipError_t launch_backward(const DevMesh& M, const BwdArgs& a_in, void* ws, cons
     auto* counter = reinterpret_cast<unsigned long long*>(base + L.counter);
     const int per1 = P.per1;
     auto* cnt = reinterpret_cast<uint32_t*>(base + L.cnt);
-    const RayOrder ord = ray_order(w.queues);
+    const RayOrder ord = ray_order(w, a.n * std::max(P.per1, 1));
     {   // walk the queries in the order of ray_bucket (region, longest first, start face)
         auto* slot = reinterpret_cast<int32_t*>(base + L.slot);
         order_rays(M, a.n, a.f, a.v, cnt, slot, ord, s);
@@ -3128,7 +3149,7 @@ hipError_t launch_backward(const DevMesh& M, const BwdArgs& a_in, void* ws, cons
     // the long walks' start states (GFD: the two short start-point steps walk
     // first, one lane each, and the start-shifted long walks begin at their
     // ends), then one persistent pass over all of them
-    const int stride = kLenClasses * ord.sub;
+    const int stride = ord.stride();
     if (per1 > 0) hipLaunchKernelGGL(k_bwd_stage1, dim3((unsigned)grid), dim3(block), 0, s, M, a, s1, per1, sh);
     if (gfd) {
         walk_short(0, 2);

@@ -100,6 +100,7 @@ struct WalkSched {
     int blocks;       // 256-lane blocks launched
     int refill_min;   // idle lanes (of 64 per ray slot) that trigger a refill
     int queues;       // ray queues: a multiple of 8, at most kMaxQueues
+    bool one_mesh;    // the handle holds one mesh (the walk order's direction classes)
 };
 
 // Persistent forward: init kernel, persistent work-queue walk, finish kernel.

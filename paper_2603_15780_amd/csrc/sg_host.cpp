@@ -31,6 +31,7 @@ struct sg_mesh_s {
     int device = 0;
     int cu_count = 0;
     int walk_blocks_per_cu = 0;
+    int bwd_blocks_per_cu = 0;
     int part_blocks_per_cu = 0;
     int64_t n_verts = 0, n_faces = 0;
     int32_t n_meshes = 1;
@@ -204,7 +205,7 @@ int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1
 }
 
 sg::WalkSched sched(const sg_opts& o, const sg_mesh_s* m) {
-    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1};
+    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1, m->cu_count, 0, false};
 }
 
 // Workspace of a call: the caller's (checked) or a stream-ordered allocation.
@@ -784,6 +785,7 @@ int sg_mesh_create(const float* X_host, int64_t n_verts, const int32_t* F_host, 
         }
     }
     m->walk_blocks_per_cu = sg::walk_blocks_per_cu();
+    m->bwd_blocks_per_cu = sg::bwd_blocks_per_cu();
     m->part_blocks_per_cu = sg::part_blocks_per_cu();
     m->n_verts = n_verts;
     m->n_faces = n_faces;
@@ -1011,7 +1013,10 @@ int sg_exp_backward_transport(sg_mesh mesh, int32_t mode, int64_t n, const int32
                                                b_out != nullptr, v_out != nullptr, status != nullptr),
                         st, ws);
     if (rc != SG_OK) return rc;
-    hipError_t e = sg::launch_backward(mesh->dev(o.boundary_mode), a, ws.p, sched(o, mesh), st);
+    sg::WalkSched w = sched(o, mesh);   // GFD's long-walk pass has its own defaults
+    if (!(opts && opts->walk_blocks > 0)) w.gfd_per_cu = mesh->bwd_blocks_per_cu;
+    w.gfd_refill = !(opts && opts->refill_min > 0);
+    hipError_t e = sg::launch_backward(mesh->dev(o.boundary_mode), a, ws.p, w, st);
     const hipError_t e2 = give_workspace(ws, st);
     if (e != hipSuccess) return hip_fail(e, "backward launch");
     if (e2 != hipSuccess) return hip_fail(e2, "workspace release");

@@ -1607,7 +1607,10 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
         if (nidle == 64 && qc.left == 0) break;
         if (qc.left > 0 && nidle >= refill_min) {
             int64_t hi = 0;
-            const int64_t base = queue_claim(counter, R, lane, nidle, qc, hi);
+            // a query's states are claimed together: they walk side by side and share the records they fetch
+            const int want = R.per > 1 && nidle >= R.per ? nidle - nidle % R.per : nidle;
+            const int64_t base = queue_claim(counter, R, lane, want, qc, hi);
+            hi = min(hi, base + want);
             bool got = false;
             if (!lane_of(act)) {
                 q = base + __popcll(idle & below);
@@ -3159,9 +3162,24 @@ hipError_t launch_backward(const DevMesh& M, const BwdArgs& a_in, void* ws, cons
         if (P.gfd_saved) walk_short(2, 1);
     }
     if (per1 > 0) {
+        // GFD's three or four long walks of a query differ by its small steps:
+        // neighbouring lanes fetch the same lines, so the pass is bound by
+        // instruction issue and latency instead of the L2's request rate.  It
+        // wants more waves than the forward, up to one state per lane (more
+        // only slow the longest walks: 30,000 queries on 20,480 faces take 128 us
+        // with two blocks per CU and 178 with six), and each refilled as a whole so
+        // that a query's walks stay side by side.  1,048,576 queries on 327,680
+        // faces, backward: 2.63 ms (three blocks per CU, refill at 32 idle lanes),
+        // 2.26 (four, 32), 2.16 (four, 48), 1.92 (six, 48), 1.79 (six, 63).
+        int blocks = w.blocks;
+        if (gfd && w.gfd_per_cu > 0) {
+            const int64_t lanes = (int64_t)per1 * a.n / (256 * (int64_t)w.cus);   // blocks per CU at one state per lane
+            blocks = w.cus * (int)std::max<int64_t>(std::min(2, w.gfd_per_cu), std::min<int64_t>(lanes, w.gfd_per_cu));
+        }
+        const int refill = gfd && w.gfd_refill ? 64 - 64 % per1 : w.refill_min;
         hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, counter);
-        SG_DISPATCH(k_walk_bwd, false, flip, dim3((unsigned)w.blocks), dim3(block), s, M, s1,
-                    QueueRanges{cnt, stride, per1}, counter, a.max_steps, a.snap, w.refill_min, w.queues);
+        SG_DISPATCH(k_walk_bwd, false, flip, dim3((unsigned)blocks), dim3(block), s, M, s1,
+                    QueueRanges{cnt, stride, per1}, counter, a.max_steps, a.snap, refill, w.queues);
     }
     if (vjp && a.mode == 0 && flip)   // (consistent orientation: k_ep_saved above)
         hipLaunchKernelGGL(k_ep_walked, dim3((unsigned)grid), dim3(block), 0, s, M, a, s1, per1);
@@ -3255,6 +3273,13 @@ hipError_t launch_ep_saved(const DevMesh& M, const BwdArgs& a, hipStream_t s) {
 int walk_blocks_per_cu() {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_walk<false, false, false>, 256, 0) != hipSuccess || nb <= 0) nb = 1;
+    return nb;
+}
+
+int bwd_blocks_per_cu() {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_walk_bwd<false, false, false>, 256, 0) != hipSuccess || nb <= 0)
+        nb = 1;
     return nb;
 }
 

@@ -101,6 +101,9 @@ struct WalkSched {
     int refill_min;   // idle lanes (of 64 per ray slot) that trigger a refill
     int queues;       // ray queues: a multiple of 8, at most kMaxQueues
     bool one_mesh;    // the handle holds one mesh (the walk order's direction classes)
+    // GFD's long-walk pass
+    int cus, gfd_per_cu;   // CUs, and the most blocks of it each holds; gfd_per_cu 0: `blocks` of them
+    bool gfd_refill;       // refills whole waves; false: refill_min
 };
 
 // Persistent forward: init kernel, persistent work-queue walk, finish kernel.
@@ -117,6 +120,7 @@ hipError_t noalloc_scratch(void** out);
 hipError_t launch_exp_persistent(const DevMesh& M, const ExpArgs& a, void* ws, const WalkSched& w, hipStream_t s,
                                  hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int walk_blocks_per_cu();
+int bwd_blocks_per_cu();
 int part_blocks_per_cu();
 
 // ---- projection integration (appendix "Projection Integration Exp Map")

@@ -139,9 +139,10 @@ void sg_mesh_destroy(sg_mesh mesh);
  * New vertex positions for an existing mesh handle (the same connectivity),
  * for optimisation loops over X (the vertex gradient of sg_exp_backward is
  * their gradient).  X_host [n_verts,3] float32 host, n_verts as at creation.
- * Re-packs the position-dependent parts in float64 on the host (edge lengths,
- * corner angles, vertex total angles, positions, mean edge) and uploads them;
- * adjacency, face order and the handle stay.  Synchronous: it waits for the
+ * Re-packs the position-dependent parts in float64 on the device (edge lengths,
+ * corner angles, vertex total angles, positions, mean edge); the first call
+ * allocates room for the new positions, kept by the handle; adjacency, face
+ * order and the handle stay.  Synchronous: it waits for the
  * device to be idle first, since no call may read the mesh while it changes.
  * A zero-area face or a non-finite position returns SG_E_DEGENERATE /
  * SG_E_ARG and leaves the mesh unchanged.

@@ -50,7 +50,8 @@ struct sg_mesh_s {
     int32_t has_flip = 0;
     size_t bytes = 0;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timed, spare;   // walk-kernel event pairs
-    sg::PackedMesh host;   // connectivity, links and face order, for sg_mesh_update_vertices
+    sg::PackedMesh host;   // connectivity and face order
+    void* d_pos = nullptr;   // sg_mesh_update_vertices: the new positions before they are accepted (kept)
     std::vector<float> hX;  // vertex positions on the host (the projection grid is built from them)
     // projection-integration Exp: per-face data in user order and one grid per
     // mesh, built on the first call that needs them (and again after a vertex update)
@@ -165,6 +166,7 @@ void free_mesh(sg_mesh_s* m) {
     (void)hipFree(m->d_geo);
     (void)hipFree(m->d_vc_off);
     (void)hipFree(m->d_vc);
+    (void)hipFree(m->d_pos);
     free_pi(m);
     delete m;
 }
@@ -710,6 +712,7 @@ int pack_geometry(const float* X_host, PackedMesh& pm) {
         for (int64_t v = 0; v < n_verts; ++v) pm.half[v] = pm.vbnd[v] ? -1 : theta_fx[v] / 2;
         pm.X.assign(X_host, X_host + 3 * n_verts);
         pm.mean_edge = esum / (double)ecount;
+        pm.n_edges = ecount;
         // 64-byte geometry records: the three vertices (w: the walk record's
         // edge lengths), its two corners and the user face id, so a start or
         // end frame takes one 64-byte segment
@@ -820,6 +823,9 @@ int sg_mesh_create(const float* X_host, int64_t n_verts, const int32_t* F_host, 
     pm.X.clear();
     pm.geo.clear();
     pm.geo.shrink_to_fit();
+    pm.face = {};   // the device holds these from here on
+    pm.half = {};
+    pm.twin = {};
     m->host = std::move(pm);
     *out = m;
     return SG_OK;
@@ -830,32 +836,50 @@ int sg_mesh_update_vertices(sg_mesh mesh, const float* X_host, int64_t n_verts) 
     if (!X_host) return fail(SG_E_ARG, "X_host is NULL");
     if (n_verts != mesh->n_verts)
         return fail(SG_E_ARG, "n_verts %lld does not match the mesh's %lld", (long long)n_verts, (long long)mesh->n_verts);
-    sg::PackedMesh& pm = mesh->host;
-    // recompute on copies so that a rejected update leaves the mesh as it was
-    const std::vector<FaceRec> face0 = pm.face;
-    const std::vector<int64_t> half0 = pm.half;
-    const double mean0 = pm.mean_edge;
-    int rc = sg::pack_geometry(X_host, pm);
-    if (rc != SG_OK) {
-        pm.face = face0;
-        pm.half = half0;
-        pm.mean_edge = mean0;
-        return rc;
+    const size_t need = sg::pos_workspace(n_verts, mesh->n_faces);
+    hipError_t e = hipSuccess;
+    if (!mesh->d_pos) {
+        e = hipMalloc(&mesh->d_pos, need);
+        if (e != hipSuccess) {
+            mesh->d_pos = nullptr;
+            return fail(SG_E_OOM, "hipMalloc(%zu): %s", need, hipGetErrorString(e));
+        }
+        mesh->bytes += need;
     }
-    hipError_t e = hipDeviceSynchronize();   // no walk may read the records while they change
+    std::vector<double> part;
+    std::vector<float> hX;
+    try {
+        part.resize(2 + (size_t)sg::pos_blocks(n_verts, mesh->n_faces));   // the error words, then the blocks' sums
+        hX.assign(X_host, X_host + 3 * n_verts);
+    } catch (const std::bad_alloc&) {
+        return fail(SG_E_OOM, "out of host memory");
+    }
+    const sg::DevMesh M = mesh->dev();
+    const uint64_t none[2] = {~0ull, ~0ull};
+    uint64_t bad[2];
+    e = hipDeviceSynchronize();   // no walk may read the records while they change
+    if (e == hipSuccess) e = hipMemcpy(mesh->d_pos, none, sizeof none, hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(sg::pos_staging(mesh->d_pos, n_verts, mesh->n_faces), X_host, (size_t)n_verts * 3 * sizeof(float),
+                      hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = sg::launch_pos_check(M, mesh->d_pos, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(part.data(), mesh->d_pos, part.size() * sizeof(double), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "vertex update");
+    std::memcpy(bad, part.data(), sizeof bad);
+    if (bad[0] != none[0]) return fail(SG_E_ARG, "vertex %lld is not finite", (long long)bad[0]);
+    if (bad[1] != none[1])
+        return fail(SG_E_DEGENERATE, "face %lld has zero area", (long long)mesh->host.order[(size_t)bad[1]]);
+    e = sg::launch_pos_commit(M, mesh->d_pos, mesh->d_vc_off, mesh->d_vc, nullptr);
     {
         std::lock_guard<std::mutex> lock(mesh->pi_mu);
         free_pi(mesh);   // the projection grid is rebuilt for the new positions on its next use
-        mesh->hX.assign(X_host, X_host + 3 * n_verts);
+        mesh->hX.swap(hX);
     }
-    if (e == hipSuccess) e = hipMemcpy(mesh->d_face, pm.face.data(), pm.face.size() * sizeof(FaceRec), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(mesh->d_half, pm.half.data(), pm.half.size() * sizeof(int64_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(mesh->d_X, X_host, (size_t)n_verts * 3 * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(mesh->d_geo, pm.geo.data(), pm.geo.size() * sizeof(float), hipMemcpyHostToDevice);
-    pm.X.clear();
-    pm.geo.clear();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return hip_fail(e, "vertex update");
-    mesh->mean_edge = pm.mean_edge;
+    double sum = 0.0;
+    for (size_t i = 2; i < part.size(); ++i) sum += part[i];
+    mesh->mean_edge = sum / (double)mesh->host.n_edges;
     return SG_OK;
 }
 

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "sg_internal.h"
@@ -80,16 +81,27 @@ struct PackedMesh {
     std::vector<int64_t> face_off;    // [n_meshes + 1] user face offsets of the batched meshes
     int64_t n_verts = 0, n_faces = 0;
     double mean_edge = 0.0;
+    int64_t n_edges = 0;              // undirected edges
     int32_t has_flip = 0;
 };
 
 // Validates and packs a mesh on the host; returns SG_OK or an SG_E_* code.
 int pack_mesh(const float* X_host, int64_t n_verts, const int32_t* F_host, int64_t n_faces,
               const int64_t* vert_offsets, const int64_t* face_offsets, int32_t n_meshes, PackedMesh& out);
-// Recomputes the position-dependent parts of a packed mesh (face records'
-// lengths and corners, half_theta, X, mean_edge) for new vertex positions,
-// keeping its connectivity, links and face order.
+// The position-dependent parts of a packed mesh (face records' lengths and
+// corners, half_theta, X, mean_edge) for its connectivity, links and face order.
 int pack_geometry(const float* X_host, PackedMesh& pm);
+
+// The same for new positions, on the device.  ws (pos_workspace bytes) holds
+// two error words (set to ~0 by the caller: the first non-finite vertex, the
+// first face without area), the blocks' sums of edge lengths, and the positions.
+inline int pos_blocks(int64_t n_verts, int64_t n_faces) { return (int)((std::max(n_verts, n_faces) + 255) / 256); }
+inline float* pos_staging(void* ws, int64_t n_verts, int64_t n_faces) {
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + 16 + 8 * (size_t)pos_blocks(n_verts, n_faces));
+}
+size_t pos_workspace(int64_t n_verts, int64_t n_faces);
+hipError_t launch_pos_check(const DevMesh& M, void* ws, hipStream_t s);
+hipError_t launch_pos_commit(const DevMesh& M, void* ws, const int32_t* vc_off, const int32_t* vc, hipStream_t s);
 
 // Plain forward: one ray per lane, run to completion (Alg. gpu_parallel).
 hipError_t launch_exp_plain(const DevMesh& M, const ExpArgs& a, hipStream_t s);

@@ -99,9 +99,16 @@ def _check(rc):
         raise SgError(rc, lib().sg_last_error().decode())
 
 
+_default_opts = None
+
+
 def opts(**kw) -> Opts:
-    o = Opts()
-    lib().sg_opts_default(C.byref(o))
+    global _default_opts
+    if _default_opts is None:
+        d = Opts()
+        lib().sg_opts_default(C.byref(d))
+        _default_opts = bytes(d)
+    o = Opts.from_buffer_copy(_default_opts)
     for k, v in kw.items():
         setattr(o, k, v)
     return o
@@ -124,12 +131,32 @@ def _np_ptr(a):
 
 
 def _dptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _with_workspace(o: Opts, need: int, dev):
+    """(opts with a workspace of `need` bytes, the tensor that holds it) for one call on the current stream.
+
+    The library's own stream-ordered allocation goes back to the driver at the next synchronisation and is mapped
+    again by the next call: 0.4 ms a call at 1M rays, 50 to 370 ms with the vertex gradient's records.  PyTorch's
+    allocator keeps the block, hands it out again in stream order, and gives it back with torch.cuda.empty_cache().
+    A caller's workspace is used as it is; if PyTorch has no memory left the library's allocation decides."""
+    import torch
+    if need == 0 or o.workspace:
+        return o, None
+    try:
+        ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    except torch.cuda.OutOfMemoryError:
+        return o, None
+    o = Opts.from_buffer_copy(o)   # (the caller's struct keeps no pointer)
+    o.workspace = ws.data_ptr()
+    o.workspace_bytes = need
+    return o, ws
 
 
 class Mesh:
@@ -238,6 +265,10 @@ class Mesh:
                 n_cross=torch.empty(n, dtype=torch.int32, device=dev) if want_cross else None,
                 hash=torch.empty(n, dtype=torch.int64, device=dev) if want_hash else None,
             )
+        ws = None   # (held until the launches are queued)
+        # (a small batch takes the plain kernel, which needs none: no query in its 16 us)
+        if not noalloc and (n > 65536 or o.kernel != KERNEL_AUTO):
+            o, ws = _with_workspace(o, self.exp_workspace_size(n, K, o), dev)
         call = lib().sg_exp_transport_noalloc if noalloc else lib().sg_exp_transport
         rc = call(
             self._h, n, _dptr(f), _dptr(b), _dptr(v), K, _dptr(W), _dptr(out["f"]), _dptr(out["b"]),
@@ -285,6 +316,7 @@ class Mesh:
         po = pi_opts(step, max_steps, search)
         gv = torch.empty(n, 3, dtype=torch.float32, device=dev)
         gb = torch.empty(n, 3, dtype=torch.float32, device=dev)
+        o, ws = _with_workspace(o, self.pi_backward_workspace_size(mode, n), dev)
         _check(lib().sg_pi_backward(self._h, int(mode), n, _dptr(f), _dptr(b), _dptr(v), _dptr(f_out), _dptr(v_out),
                                     _dptr(g), _dptr(gv), _dptr(gb), C.byref(po), C.byref(o), _stream()))
         return gv, gb
@@ -293,6 +325,11 @@ class Mesh:
         nb = C.c_size_t()
         _check(lib().sg_pi_backward_workspace_size(self._h, int(mode), n, C.byref(nb)))
         return nb.value
+
+    def _backward_workspace(self, o, mode, n, want_vjp, grad_X, dev):
+        if mode == BWD_EP and grad_X is None:   # none on meshes whose faces agree in orientation
+            return o, None
+        return _with_workspace(o, self.backward_workspace_size(mode, n, want_vjp, grad_X is not None, o), dev)
 
     def backward(self, mode, f, b, v, g, *, f_out=None, b_out=None, v_out=None, status=None, out=None, grad_X=None,
                  want_vjp=True, g_b=None, g_v=None, g_W=None, o: Opts | None = None, **kw):
@@ -325,6 +362,7 @@ class Mesh:
             gW_ = torch.empty(n, K, 3, dtype=torch.float32, device=dev) if g_W is not None else None
             if grad_X is not None:
                 assert grad_X.dtype == torch.float64 and grad_X.is_contiguous() and grad_X.shape == (self.n_verts, 3)
+            o, ws = self._backward_workspace(o, mode, n, True, grad_X, dev)
             _check(lib().sg_exp_backward_transport(
                 self._h, int(mode), n, _dptr(f), _dptr(b), _dptr(v), K, _dptr(f_out), _dptr(b_out), _dptr(v_out),
                 _dptr(status),
@@ -341,6 +379,7 @@ class Mesh:
             out = (None, None)
         elif out is None:
             out = (torch.empty(n, 3, dtype=torch.float32, device=dev), torch.empty(n, 3, dtype=torch.float32, device=dev))
+        o, ws = self._backward_workspace(o, mode, n, want_vjp, grad_X, dev)
         _check(lib().sg_exp_backward(self._h, int(mode), n, _dptr(f), _dptr(b), _dptr(v), _dptr(f_out), _dptr(b_out),
                                      _dptr(v_out), _dptr(status), _dptr(g), _dptr(out[0]), _dptr(out[1]), _dptr(grad_X), C.byref(o),
                                      _stream()))

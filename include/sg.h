@@ -325,9 +325,8 @@ int sg_backward_workspace_size(sg_mesh mesh, int32_t mode, int64_t n, int32_t wa
  * v); n_steps[n] int32 (nullable) receives the projection steps taken.
  * status: SG_RAY_OK, SG_RAY_MAXSTEPS (l still short after max_steps steps),
  * SG_RAY_BADINPUT.  The first PI call on a handle, and the first after
- * sg_mesh_update_vertices, builds the per-face records and grids on the host
- * and uploads them (synchronous; about 100 bytes per face plus 4 bytes per
- * cell).  Float32 arithmetic; the traced length is summed in float-float.
+ * sg_mesh_update_vertices, builds the per-face records and grids on the device
+ * (synchronous; about 100 bytes per face plus 4 bytes per cell).  Float32 arithmetic; the traced length is summed in float-float.
  */
 enum { SG_PI_GRID = 0, SG_PI_SCAN = 1 };
 typedef struct {

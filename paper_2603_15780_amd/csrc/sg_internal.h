@@ -95,10 +95,13 @@ static_assert(sizeof(PiFace) == 64, "PiFace is one 64-byte segment");
 
 // Uniform grid over one mesh of a handle: cell (ix, iy, iz) covers
 // [o + i h, o + (i + 1) h] per axis (evaluated in float64) and lists every
-// face whose bounding box, widened by a margin, meets it.  A nearest-point
-// search visits cells in rings around the query's cell and skips those
-// farther than the best distance found, so it returns what a scan over every
-// face would.
+// face whose bounding box, widened by kPiCover h, meets it.  A nearest-point
+// search looks through the query's cell, which settles it while the nearest
+// face is within kPiCover h of the cell's (the widening lengthens the lists by a
+// quarter; without it most waves had a lane that needed a second cell), else
+// through every cell within the best distance found, so it returns what a scan
+// over every face would.
+constexpr double kPiCover = 0.1;
 struct PiGrid {
     float ox, oy, oz, h;      // origin and cell size
     int32_t nx, ny, nz;       // cells per axis

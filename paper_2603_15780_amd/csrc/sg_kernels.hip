@@ -2920,6 +2920,14 @@ __global__ __launch_bounds__(256) void k_pos_vertices(DevMesh M, const float* X,
 
 }  // namespace
 
+hipError_t launch_scan(uint32_t* x, int64_t n, uint32_t* tile, hipStream_t s) {
+    const int64_t nt = scan_tiles(n);
+    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nt), dim3(1024), 0, s, x, n, tile);
+    hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, tile, (int)nt);
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, n, (const uint32_t*)tile);
+    return hipGetLastError();
+}
+
 size_t pos_workspace(int64_t n_verts, int64_t n_faces) {
     return 16 + 8 * (size_t)pos_blocks(n_verts, n_faces) + 12 * (size_t)n_verts;
 }
@@ -3187,7 +3195,7 @@ static BwdLayout bwd_layout(int64_t n, const BwdPlan& P, bool gradx, int64_t n_f
     L.sterm = o; o = align256(o + (gradx ? 9 * (size_t)n * sizeof(float) : 0));
     L.srank = o; o = align256(o + (gradx ? (size_t)n * sizeof(int32_t) : 0));
     L.fstart = o; o = align256(o + (gradx ? ((size_t)n_faces + 1) * sizeof(uint32_t) : 0));
-    L.ftile = o; o = align256(o + (gradx ? (((size_t)n_faces + 1 + 4095) / 4096) * sizeof(uint32_t) : 0));
+    L.ftile = o; o = align256(o + (gradx ? (size_t)scan_tiles(n_faces + 1) * sizeof(uint32_t) : 0));
     L.qlist = o; o = align256(o + (gradx ? (size_t)n * sizeof(int32_t) : 0));
     L.slot = o; o = align256(o + (walk ? (size_t)n * sizeof(int32_t) : 0));
     L.cnt = o; o = align256(o + (walk ? (size_t)kCountWords * sizeof(uint32_t) : 0));
@@ -3321,12 +3329,7 @@ hipError_t launch_backward(const DevMesh& M, const BwdArgs& a_in, void* ws, cons
                            P.gx_saved ? (const StateRec*)nullptr : (const StateRec*)s1, per1, s3, cvec, sterm, srank,
                            fstart);
         // each start face's queries as one list (counts to offsets, then the ranks place them)
-        const int64_t ntile = (nfs + 4095) / 4096;
-        auto* tile = reinterpret_cast<uint32_t*>(base + L.ftile);
-        hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntile), dim3(1024), 0, s, fstart, nfs, tile);
-        hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, s, tile, (int)ntile);
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((nfs + block - 1) / block)), dim3(block), 0, s, fstart, nfs,
-                           (const uint32_t*)tile);
+        (void)launch_scan(fstart, nfs, reinterpret_cast<uint32_t*>(base + L.ftile), s);
         hipLaunchKernelGGL(k_gradx_start_place, dim3((unsigned)grid), dim3(block), 0, s, M, a);
         hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, counter);
         const int64_t nh = 3 * M.n_faces;

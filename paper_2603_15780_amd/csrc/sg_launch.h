@@ -92,6 +92,10 @@ int pack_mesh(const float* X_host, int64_t n_verts, const int32_t* F_host, int64
 // corners, half_theta, X, mean_edge) for its connectivity, links and face order.
 int pack_geometry(const float* X_host, PackedMesh& pm);
 
+// Exclusive prefix sums of x[0, n) in place; tile: scan_tiles(n) words of scratch.
+inline int64_t scan_tiles(int64_t n) { return (n + 4095) / 4096; }
+hipError_t launch_scan(uint32_t* x, int64_t n, uint32_t* tile, hipStream_t s);
+
 // The same for new positions, on the device.  ws (pos_workspace bytes) holds
 // two error words (set to ~0 by the caller: the first non-finite vertex, the
 // first face without area), the blocks' sums of edge lengths, and the positions.
@@ -158,6 +162,17 @@ struct PiArgsT {
 };
 using PiArgs = PiArgsT<float>;
 hipError_t launch_pi_exp(const PiMesh& P, const PiArgs& a, hipStream_t s);
+// The projection data of a handle, in three parts.  Extents: kPiParts partial
+// results per mesh (lowest and highest coordinates, sum of edge lengths, largest
+// absolute coordinate of a share of all vertices).  Faces and counts: the face
+// records, and at cells[c] the entries before cell c (cells[total]: all of
+// them; tile: scan_tiles(total + 1) words; sum: their number in 64 bits).  Fill: the entries; cells[c] moves
+// to the end of cell c, so that cells - 1 (a zero word) are the cells' starts.
+constexpr int kPiParts = 16, kPiExtent = 8;
+hipError_t launch_pi_extents(const DevMesh& M, const int64_t* face_off, int n_meshes, double* out, hipStream_t s);
+hipError_t launch_pi_count(const DevMesh& M, const PiMesh& P, PiFace* face, uint32_t* cells, int64_t total, double pad,
+                           uint32_t* tile, unsigned long long* sum, hipStream_t s);
+hipError_t launch_pi_fill(const PiMesh& P, uint32_t* cells, int32_t* cell_face, double pad, hipStream_t s);
 // EP (saved f', v') or GFD (seven PI walks per query, stacked in two launches).
 size_t pi_bwd_workspace(int64_t n, int32_t mode);
 hipError_t launch_pi_backward(const PiMesh& P, const DevMesh& M, const BwdArgs& a, const PiArgs& pa, void* ws,

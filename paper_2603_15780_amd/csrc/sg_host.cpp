@@ -1185,8 +1185,23 @@ int sg_pi_exp(sg_mesh mesh, int64_t n, const int32_t* f, const float* b, const f
     a.step = po.step;
     a.max_steps = po.max_steps;
     a.scan = po.search == SG_PI_SCAN;
-    hipError_t e = sg::launch_pi_exp(mesh->pi(), a, (hipStream_t)stream);
+    // a large batch takes its rays in a spatial order; without room for it, or while a graph is recorded
+    // (which would keep the allocation), they go as they come, with the same results
+    const hipStream_t st = (hipStream_t)stream;
+    Workspace ws;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!a.scan && sg::pi_ordered(n, mesh->n_faces) && n < ((int64_t)1 << 31) && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+        cap == hipStreamCaptureStatusNone) {
+        ws.own = hipMallocAsync(&ws.p, sg::pi_order_workspace(n), st) == hipSuccess;
+        if (!ws.own) {
+            ws.p = nullptr;
+            (void)hipGetLastError();
+        }
+    }
+    hipError_t e = sg::launch_pi_exp(mesh->pi(), mesh->dev(), a, ws.p, st);
+    const hipError_t e2 = give_workspace(ws, st);
     if (e != hipSuccess) return hip_fail(e, "PI launch");
+    if (e2 != hipSuccess) return hip_fail(e2, "workspace release");
     return SG_OK;
 }
 

@@ -159,9 +159,18 @@ struct PiArgsT {
     double step;        // s
     int32_t max_steps;
     int32_t scan;       // 1: scan every face of the mesh (the printed form), 0: grid search
+    const int32_t* order;   // grid search: the order to take the rays in, or null
 };
 using PiArgs = PiArgsT<float>;
-hipError_t launch_pi_exp(const PiMesh& P, const PiArgs& a, hipStream_t s);
+// ws: pi_order_workspace(n) bytes for a spatial order of the rays, or null (as
+// they come).  The order pays once the face records exceed one L2 (4 MB) and
+// there are enough rays for more than half a wave per SIMD (below, a step waits for its own
+// loads): 131,072 rays on 20,480 faces take 1.60 ms ordered, 1.56 not.
+inline bool pi_ordered(int64_t rows, int64_t n_faces) {
+    return rows >= 32768 && n_faces * (int64_t)sizeof(PiFace) >= ((int64_t)4 << 20);
+}
+size_t pi_order_workspace(int64_t n);
+hipError_t launch_pi_exp(const PiMesh& P, const DevMesh& M, const PiArgs& a, void* ws, hipStream_t s);
 // The projection data of a handle, in three parts.  Extents: kPiParts partial
 // results per mesh (lowest and highest coordinates, sum of edge lengths, largest
 // absolute coordinate of a share of all vertices).  Faces and counts: the face

@@ -93,9 +93,10 @@ typedef struct {
                               bit 3 (sg_autotune): tune again even for a cached class of batches */
     int32_t refill_min;    /* persistent kernel: a wave refetches rays once this many of its 64 lanes are
                               idle (of 128 ray slots with two rays per lane); <= 0: 48 per 64 slots in
-                              the forward, 32 in the backward's walks (GFD's long walks: whole waves) */
+                              the forward, 32 in the backward's walks (GFD's long walks: whole waves, the
+                              vertex gradient: 48) */
     int32_t walk_blocks;   /* persistent kernel: 256-lane blocks launched; <= 0: three per CU (GFD's long walks:
-                              as many as fit) */
+                              as many as fit; the vertex gradient: one to three by the batch) */
     int32_t rays_per_lane; /* persistent kernel: rays each lane walks at once, 1 or 2; <= 0: tuned default */
     int32_t ray_queues;    /* persistent kernel: ray queues the walk claims rays from, a multiple of 8 (an
                               equal share of each XCD, which drains its queues one after another) up to 64;
@@ -103,9 +104,9 @@ typedef struct {
     int32_t boundary_mode; /* SG_BOUNDARY_STOP (default) or SG_BOUNDARY_AVOID; honoured by every kernel and
                               the backward (the vertex gradient leaves out rays that slid) */
     int32_t gradx_records; /* vertex gradient: edge crossings per query for which the workspace holds records
-                              (48 bytes each, at most 2^30 records per call) that are summed per half-edge in
-                              LDS; crossings past them add their sums with float64 atomics (same result,
-                              slower).  0: 256; < 0: none */
+                              (48 bytes each, at most 2^30 records per call; up to 4,194,304 half-edges twice
+                              as many of 24 bytes) that are summed per half-edge in LDS; crossings past them
+                              add their sums with float64 atomics (same result, slower).  0: 256; < 0: none */
     void* workspace;       /* optional caller-owned device workspace, 256-byte aligned, at least the size
                               sg_exp_workspace_size / sg_backward_workspace_size report.  With it a call
                               allocates nothing, so it can be captured in a HIP graph (debug bit 2 aside).

@@ -206,7 +206,8 @@ int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1
 }
 
 sg::WalkSched sched(const sg_opts& o, const sg_mesh_s* m) {
-    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1, m->cu_count, 0, false};
+    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1, false, false, m->cu_count,
+                         m->bwd_blocks_per_cu};
 }
 
 // Workspace of a call: the caller's (checked) or a stream-ordered allocation.
@@ -249,11 +250,14 @@ int check_bwd_opts(const sg_opts* in, sg_opts& o, sg_mesh m) {
     return rc;
 }
 
+// Whether the caller leaves the backward's block counts to the library.
+bool own_blocks(const sg_opts* opts) { return !(opts && opts->walk_blocks > 0); }
+
 // have_*: which saved forward outputs the call is given (none: the size that covers every call)
-size_t bwd_workspace_bytes(const sg_opts& o, sg_mesh m, int64_t n, int32_t mode, bool vjp, bool gradx,
+size_t bwd_workspace_bytes(const sg_opts& o, bool own, sg_mesh m, int64_t n, int32_t mode, bool vjp, bool gradx,
                            bool have_f = false, bool have_b = false, bool have_v = false, bool have_status = false) {
     return sg::bwd_workspace(n, mode, m->has_flip != 0, vjp, gradx, m->n_faces, o.gradx_records, o.walk_blocks,
-                             o.boundary_mode != SG_BOUNDARY_STOP, have_f, have_b, have_v, have_status);
+                             own ? m->cu_count : 0, o.boundary_mode != SG_BOUNDARY_STOP, have_f, have_b, have_v, have_status);
 }
 
 size_t exp_workspace_bytes(const sg_opts& o, int64_t n, int32_t K) {
@@ -979,13 +983,13 @@ int sg_exp_backward_transport(sg_mesh mesh, int32_t mode, int64_t n, const int32
     a.gx_records = o.gradx_records;
     a.vc_off = mesh->d_vc_off;
     a.vc = mesh->d_vc;
-    rc = take_workspace(o, bwd_workspace_bytes(o, mesh, n, mode, vjp, a.grad_X != nullptr, f_out != nullptr,
+    rc = take_workspace(o, bwd_workspace_bytes(o, own_blocks(opts), mesh, n, mode, vjp, a.grad_X != nullptr, f_out != nullptr,
                                                b_out != nullptr, v_out != nullptr, status != nullptr),
                         st, ws);
     if (rc != SG_OK) return rc;
-    sg::WalkSched w = sched(o, mesh);   // GFD's long-walk pass has its own defaults
-    if (!(opts && opts->walk_blocks > 0)) w.gfd_per_cu = mesh->bwd_blocks_per_cu;
-    w.gfd_refill = !(opts && opts->refill_min > 0);
+    sg::WalkSched w = sched(o, mesh);   // GFD's long-walk pass and the adjoint walk have their own defaults
+    w.own_blocks = own_blocks(opts);
+    w.own_refill = !(opts && opts->refill_min > 0);
     hipError_t e = sg::launch_backward(mesh->dev(o.boundary_mode), a, ws.p, w, st);
     const hipError_t e2 = give_workspace(ws, st);
     if (e != hipSuccess) return hip_fail(e, "backward launch");
@@ -1022,7 +1026,7 @@ int sg_backward_workspace_size(sg_mesh mesh, int32_t mode, int64_t n, int32_t wa
     int rc = check_bwd_opts(opts, o, mesh);
     if (rc != SG_OK) return rc;
     *bytes = (n == 0 || (!want_vjp && !want_grad_X)) ? 0
-                                                     : bwd_workspace_bytes(o, mesh, n, mode, want_vjp != 0,
+                                                     : bwd_workspace_bytes(o, own_blocks(opts), mesh, n, mode, want_vjp != 0,
                                                                            want_grad_X != 0);
     return SG_OK;
 }

@@ -117,9 +117,9 @@ struct WalkSched {
     int refill_min;   // idle lanes (of 64 per ray slot) that trigger a refill
     int queues;       // ray queues: a multiple of 8, at most kMaxQueues
     bool one_mesh;    // the handle holds one mesh (the walk order's direction classes)
-    // GFD's long-walk pass
-    int cus, gfd_per_cu;   // CUs, and the most blocks of it each holds; gfd_per_cu 0: `blocks` of them
-    bool gfd_refill;       // refills whole waves; false: refill_min
+    // the backward's walks: their own block counts and refill thresholds, or those above
+    bool own_blocks, own_refill;
+    int cus, gfd_per_cu;   // CUs, and the most blocks of GFD's long-walk pass each holds
 };
 
 // Persistent forward: init kernel, persistent work-queue walk, finish kernel.
@@ -192,7 +192,7 @@ hipError_t launch_ep_saved(const DevMesh& M, const BwdArgs& a, hipStream_t s);
 // Backward of the exponential map (extrinsic proxy or geodesic finite differences).
 // have_*: which of the forward's saved outputs (f', b', v', status) the call is given.
 size_t bwd_workspace(int64_t n, int32_t mode, bool has_flip, bool vjp, bool gradx, int64_t n_faces,
-                     int32_t gx_records, int walk_blocks, bool hole, bool have_f, bool have_b, bool have_v,
+                     int32_t gx_records, int walk_blocks, int cus, bool hole, bool have_f, bool have_b, bool have_v,
                      bool have_status);
 hipError_t launch_backward(const DevMesh& M, const BwdArgs& a, void* ws, const WalkSched& w, hipStream_t s);
 

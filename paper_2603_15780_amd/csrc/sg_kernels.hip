@@ -830,7 +830,7 @@ SG_HD __forceinline__ FaceWords face_words(const FaceRec& r) {
 // fraction mu of that edge from its non-apex end (omu: from the apex).
 struct Exit {
     uint64_t mca, m0, m2;   // lanes that leave through c-a; whose entry edge is 0, is 2
-    uint32_t A, B;          // corners at a and b
+    uint32_t turn;          // what the crossing adds to the direction's angle
     float cx, cy;           // apex in the entry chart
     float lam, mu, omu;
 };
@@ -845,17 +845,17 @@ SG_HD __forceinline__ void find_exit(const FaceWords& q, const Ray& st, float sn
     const uint32_t c0 = q.c0, c1 = q.c1, c2 = kPiFx - (q.c0 + q.c1);
     // the entry edge index, tested on the word itself (its top field)
     const bool k0 = (uint32_t)st.h < (1u << kHeShift), k2 = (uint32_t)st.h >= (2u << kHeShift);
-    x.A = k0 ? c0 : (k2 ? c2 : c1);
-    x.B = k0 ? c1 : (k2 ? c0 : c2);
+    const uint32_t A = k0 ? c0 : (k2 ? c2 : c1), B = k0 ? c1 : (k2 ? c0 : c2);   // corners at a and b
     const float lac = k0 ? l2 : (k2 ? l1 : l0);
     float sA, cA;
-    sincos_fx(x.A, sA, cA);
+    sincos_fx(A, sA, cA);
     x.cx = lac * cA;
     x.cy = lac * sA;
     const float cross = fmaf(cs, x.cy, -sn * (x.cx - st.s));   // > 0: apex left of the ray
     x.m0 = lane_mask(k0);
     x.m2 = lane_mask(k2);
     x.mca = lane_mask(cross < -st.bias);
+    x.turn = lane_of(x.mca) ? 0u - A : B;
     const float w = lane_of(x.mca) ? st.s : st.t;
     const float acr = fabsf(cross);
     const float rD = rcp(fmaf(w, sn, acr));
@@ -870,7 +870,7 @@ template <bool kHash, bool kFlip>
 SG_HD __forceinline__ void cross_edge(const DevMesh& M, const Exit& x, float len, int32_t nx, Ray& st) {
     const bool via_ca = lane_of(x.mca);
     const float dm = x.mu * len, dom = x.omu * len;
-    uint32_t ph = st.phi + (via_ca ? 0u - x.A : x.B);
+    uint32_t ph = st.phi + x.turn;
     st.s = via_ca ? dm : dom;
     st.t = via_ca ? dom : dm;
     if (kFlip) {   // neighbour traverses the edge the same way: mirror the chart
@@ -961,13 +961,18 @@ SG_HD __forceinline__ int odd_step(const DevMesh& M, Ray& st, int32_t max_steps,
 // 237 us (the plain kernel), 1,048,576 from 1.101 to 1.091 ms, and the finite
 // differences of 1,048,576 queries, whose neighbouring lanes share lines, from
 // 2.83 to 2.77 ms.
+// q holds st.h's record and is left with the next face's, loaded as soon as
+// the exit edge is known, so that the rest of the step and the next angle's sine
+// run while it is on its way: 65,536 rays 231 -> 180 us, 1,048,576 1.030 ->
+// 1.003 ms (200,003 on a mesh with holes 392 -> 366 us).  Everything else that
+// the step takes from the record is picked before that load; with copies of it
+// kept past the load the wait came before the sine, and 65,536 rays took 202 us.
 // Lanes that are not alive (a slot without a ray holds a dummy state) do
 // nothing.  kPre: the caller passes sin and cos of st.phi (psn, pcs).  kDefer:
 // an odd step is left to the caller (kStepOdd, the state unchanged).
 template <bool kHash, bool kFlip, bool kHole, bool kPre = false, bool kDefer = false>
-SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps, float snap, Final& fin,
+SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int32_t max_steps, float snap, Final& fin,
                                    bool alive = true, float psn = 0.f, float pcs = 0.f) {
-    const FaceWords q = face_words(face_rec(M, st.h));
     float sn, cs;
     if constexpr (kPre) {
         sn = psn;
@@ -982,13 +987,18 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps
     const float l0 = q.l0, l1 = q.l1, l2 = q.l2;
     const int32_t n0 = q.n0, n1 = q.n1, n2 = q.n2;
     const int32_t nx = e0 ? n0 : (e1 ? n1 : n2);
+    float len = e0 ? l0 : (e1 ? l1 : l2);
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(len), "+v"(x.turn));   // picked here: the new record takes the old one's registers
+#endif
+    q = face_words(face_rec(M, max(nx, 0)));   // (no neighbour: any face)
     const float Lr = st.Lhi + st.Llo;
     const uint64_t live = lane_mask(alive);
     const uint64_t m_end = lane_mask(!(x.lam < Lr)) & live;   // ends inside this face (ties stay in the face)
     const uint64_t m_odd = (lane_mask(st.ncross >= max_steps) | lane_mask(x.mu < snap) | lane_mask(x.omu < snap) |
                             lane_mask(nx < 0)) & ~m_end & live;
     if (lane_of(live & ~(m_end | m_odd)))
-        cross_edge<kHash, kFlip>(M, x, e0 ? l0 : (e1 ? l1 : l2), nx, st);
+        cross_edge<kHash, kFlip>(M, x, len, nx, st);
     int ev = kStepContinue;
     if (lane_of(m_end)) {
         set_final(fin, st, fmaf(Lr, cs, st.s), Lr * sn, kRayOk);
@@ -997,7 +1007,10 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps
     if constexpr (kDefer) {
         if (lane_of(m_odd)) ev = kStepOdd;
     } else if (__builtin_expect(m_odd != 0ull, 0)) {
-        if (lane_of(m_odd)) ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
+        if (lane_of(m_odd)) {
+            ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
+            if (ev == kStepContinue) q = face_words(face_rec(M, st.h));
+        }
     }
     return ev;
 }
@@ -1011,11 +1024,14 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, Ray& st, int32_t max_steps
 constexpr int kParkMin = 16;
 
 template <bool kHash, bool kFlip, bool kHole>
-SG_HD __forceinline__ int take_parked(const DevMesh& M, uint64_t act, uint64_t& park, int ev, Ray& st, int32_t max_steps,
-                                      float snap, Final& fin) {
+SG_HD __forceinline__ int take_parked(const DevMesh& M, uint64_t act, uint64_t& park, int ev, FaceWords& q, Ray& st,
+                                      int32_t max_steps, float snap, Final& fin) {
     park |= lane_mask(ev == kStepOdd);
     if (park != 0ull && (__builtin_popcountll(park) >= kParkMin || (act & ~park) == 0ull)) {
-        if (lane_of(park)) ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
+        if (lane_of(park)) {
+            ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
+            if (ev == kStepContinue) q = face_words(face_rec(M, st.h));
+        }
         park = 0ull;
     }
     return ev;
@@ -1023,16 +1039,17 @@ SG_HD __forceinline__ int take_parked(const DevMesh& M, uint64_t act, uint64_t& 
 
 template <bool kHash, bool kFlip, bool kHole>
 SG_HD __forceinline__ void walk_to_end(const DevMesh& M, Ray& st, int32_t max_steps, float snap, Final& fin) {
+    FaceWords q = face_words(face_rec(M, st.h));
     if constexpr (kHole) {   // (the lanes that are here, as one wave)
         uint64_t act = lane_mask(true), park = 0ull;
         while (act != 0ull) {
             int ev = kStepContinue;
-            if (lane_of(act & ~park)) ev = walk_step<kHash, kFlip, true, false, true>(M, st, max_steps, snap, fin);
-            ev = take_parked<kHash, kFlip, true>(M, act, park, ev, st, max_steps, snap, fin);
+            if (lane_of(act & ~park)) ev = walk_step<kHash, kFlip, true, false, true>(M, q, st, max_steps, snap, fin);
+            ev = take_parked<kHash, kFlip, true>(M, act, park, ev, q, st, max_steps, snap, fin);
             act &= ~lane_mask(ev == kStepDone);
         }
     } else {
-        while (walk_step<kHash, kFlip, false>(M, st, max_steps, snap, fin) == kStepContinue) {
+        while (walk_step<kHash, kFlip, false>(M, q, st, max_steps, snap, fin) == kStepContinue) {
         }
     }
 }
@@ -1806,6 +1823,7 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
     int32_t ray = 0;   // with fin_out: the query index, carried in the initial state's crossing count
     Ray st;
     st.h = 0; st.s = st.t = st.Lhi = st.Llo = st.bias = 0.f; st.phi = st.par = 0u; st.ncross = 0; st.hash = 0ull;
+    FaceWords wq{};   // the face record of st.h
     float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
     float gsn = 0.f, gcs = 0.f;   // with kGX: sin and cos of st.phi, shared by the crossing's terms and the next step
     for (;;) {
@@ -1825,6 +1843,7 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
                     const StateRec rec = states[q];
                     if (rec.h >= 0) {
                         unpack_state(rec, st);
+                        wq = face_words(face_rec(M, st.h));
                         if (fin_out) {
                             ray = rec.ncross;
                             st.ncross = 0;
@@ -1858,12 +1877,12 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
                 Final fin;
                 int ev = -1;   // (a lane without a ray, or parked)
                 if (lane_of(act & ~park))
-                    ev = walk_step<kHash, kFlip, true, kGX, true>(M, st, max_steps, snap, fin, true, gsn, gcs);
-                ev = take_parked<kHash, kFlip, true>(M, act, park, ev, st, max_steps, snap, fin);
+                    ev = walk_step<kHash, kFlip, true, kGX, true>(M, wq, st, max_steps, snap, fin, true, gsn, gcs);
+                ev = take_parked<kHash, kFlip, true>(M, act, park, ev, wq, st, max_steps, snap, fin);
                 if (ev == kStepDone || ev == kStepContinue) settle(ev, fin);
             } else if (lane_of(act)) {
                 Final fin;
-                const int ev = walk_step<kHash, kFlip, false, kGX>(M, st, max_steps, snap, fin, true, gsn, gcs);
+                const int ev = walk_step<kHash, kFlip, false, kGX>(M, wq, st, max_steps, snap, fin, true, gsn, gcs);
                 settle(ev, fin);
             }
             act &= ~lane_mask(done);
@@ -1946,6 +1965,7 @@ __device__ __forceinline__ void walk_loop2(const DevMesh& M, StateRec* states, Q
     QueueCursor qc = queue_start(nq);
     int64_t q0 = 0, q1 = 0;
     Ray s0, s1;
+    FaceWords g0{}, g1{};
     s0.h = 0; s0.s = s0.t = s0.Lhi = s0.Llo = s0.bias = 0.f; s0.phi = s0.par = 0u; s0.ncross = 0; s0.hash = 0ull;
     s1 = s0;
     for (;;) {
@@ -1978,11 +1998,13 @@ __device__ __forceinline__ void walk_loop2(const DevMesh& M, StateRec* states, Q
                 }
             }
         }
+        g0 = face_words(face_rec(M, s0.h));
+        g1 = face_words(face_rec(M, s1.h));
         const int stop_at = qc.left == 0 ? 128 : refill_min;
         for (;;) {
             Final f0, f1;
-            const int e0 = walk_step<kHash, kFlip, kHole>(M, s0, max_steps, snap, f0, a0);
-            const int e1 = walk_step<kHash, kFlip, kHole>(M, s1, max_steps, snap, f1, a1);
+            const int e0 = walk_step<kHash, kFlip, kHole>(M, g0, s0, max_steps, snap, f0, a0);
+            const int e1 = walk_step<kHash, kFlip, kHole>(M, g1, s1, max_steps, snap, f1, a1);
             if (a0 && e0 == kStepDone) {
                 *reinterpret_cast<Final*>(&states[q0]) = f0;
                 a0 = false;
@@ -2427,6 +2449,7 @@ __global__ __launch_bounds__(256) void k_walk_round(DevMesh M, StateRec* states,
     bool active = false, exhausted = false;
     int list_n = 0, list_pos = 0;
     int32_t ray = 0;
+    FaceWords wq{};
     Ray st;
     st.h = 0; st.s = st.t = st.Lhi = st.Llo = st.bias = 0.f; st.phi = st.par = 0u; st.ncross = 0; st.hash = 0ull;
     for (;;) {
@@ -2459,6 +2482,7 @@ __global__ __launch_bounds__(256) void k_walk_round(DevMesh M, StateRec* states,
                 if (k < list_n) {
                     ray = list[k];
                     unpack_state(states[ray], st);
+                    wq = face_words(face_rec(M, st.h));
                     st.hash = kHash ? hashes[ray] : 0ull;
                     active = true;
                 }
@@ -2469,7 +2493,7 @@ __global__ __launch_bounds__(256) void k_walk_round(DevMesh M, StateRec* states,
         for (;;) {
             if (active) {
                 Final fin;
-                if (walk_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin) == kStepDone) {
+                if (walk_step<kHash, kFlip, kHole>(M, wq, st, max_steps, snap, fin) == kStepDone) {
                     *reinterpret_cast<Final*>(&states[ray]) = fin;
                     tags[ray] = kTagDone;
                     active = false;

@@ -266,40 +266,20 @@ size_t exp_workspace_bytes(const sg_opts& o, int64_t n, int32_t K) {
                                              : sg::exp_persistent_workspace(n, K);
 }
 
-// Builds the projection-integration data of a handle on the device: per-face
-// records in user order and one uniform grid per mesh whose cells list the faces
-// whose bounding boxes, widened by a margin, meet them.  Cells are one mean edge
-// wide (wider if a mesh would need more than 32 cells per face): against 1.5
-// edges a query's cell lists 11 faces instead of 18 on a smooth mesh (131,072
-// rays on 327,680 faces: 2.58 ms, 3.05 with 1.25 edges, 3.65 with 1.5).
-// Called with pi_mu held; on failure the caller frees what was allocated.
-int build_pi(sg_mesh m) {
-    const sg::PackedMesh& pm = m->host;
-    const std::vector<int64_t>& fo = pm.face_off;
-    const int nm = (int)fo.size() - 1;
-    const sg::DevMesh M = m->dev();
-    // extents of each mesh
-    std::vector<double> ext((size_t)nm * sg::kPiParts * sg::kPiExtent);
-    const size_t off_bytes = (fo.size() * sizeof(int64_t) + 255) & ~(size_t)255;
-    void* tmp = nullptr;
-    hipError_t e = hipMalloc(&tmp, off_bytes + ext.size() * sizeof(double));
-    if (e != hipSuccess) return fail(SG_E_OOM, "hipMalloc: %s", hipGetErrorString(e));
-    double* d_ext = reinterpret_cast<double*>(reinterpret_cast<char*>(tmp) + off_bytes);
-    e = hipMemcpy(tmp, fo.data(), fo.size() * sizeof(int64_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = sg::launch_pi_extents(M, reinterpret_cast<const int64_t*>(tmp), nm, d_ext, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
-    (void)hipFree(tmp);
-    if (e != hipSuccess) return hip_fail(e, "projection extents");
-    double scale = 1.0;
-    std::vector<sg::PiGrid> grid(nm);
+// One uniform grid per mesh from its extents, in cells of `edges` mean edges
+// (wider if a mesh would need more than cell_cap cells per face).  Returns the
+// number of cells, and the largest absolute coordinate (at least 1) in scale.
+uint64_t pi_grids(const std::vector<int64_t>& fo, const std::vector<double>& ext, double edges, int64_t cell_cap,
+                  std::vector<sg::PiGrid>& grid, double& scale) {
     uint64_t total = 0;
-    for (int k = 0; k < nm; ++k) {
+    scale = 1.0;
+    for (size_t k = 0; k < grid.size(); ++k) {
         sg::PiGrid& G = grid[k];
         G.face0 = (int32_t)fo[k];
         G.face1 = (int32_t)fo[k + 1];
         double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY}, el = 0.0;
         for (int p = 0; p < sg::kPiParts; ++p) {
-            const double* v = &ext[((size_t)k * sg::kPiParts + p) * sg::kPiExtent];
+            const double* v = &ext[(k * sg::kPiParts + p) * sg::kPiExtent];
             for (int c = 0; c < 3; ++c) {
                 mn[c] = std::min(mn[c], v[c]);
                 mx[c] = std::max(mx[c], v[3 + c]);
@@ -312,9 +292,9 @@ int build_pi(sg_mesh m) {
             for (int c = 0; c < 3; ++c) mn[c] = mx[c] = 0.0;
             el = 3.0;
         }
-        double h = el / (3.0 * (double)std::max<int64_t>(fm, 1));
+        double h = edges * el / (3.0 * (double)std::max<int64_t>(fm, 1));
         if (!(h > 0.0)) h = 1.0;
-        const double cap = (double)std::max<int64_t>(32 * fm, 4096);
+        const double cap = (double)std::max<int64_t>(cell_cap * fm, 4096);
         int32_t n[3];
         double o[3];
         for (;;) {
@@ -336,33 +316,74 @@ int build_pi(sg_mesh m) {
         G.nz = n[2];
         G.cell0 = (uint32_t)total;
         total += (uint64_t)n[0] * n[1] * n[2];
-        if (total >= ((uint64_t)1 << 31)) return fail(SG_E_OOM, "projection grid too large");
     }
-    // distances within 1e-12 of the largest coordinate are one nearest point (float64 rounding);
-    // the cell search reaches 1e-9 further, past any rounding of a box distance
-    m->pi_tie = 1e-12 * scale;
-    m->pi_slack = 1e-9 * scale;
-    const double pad = scale * std::ldexp(1.0, -20);
+    return total;
+}
+
+// Builds the projection-integration data of a handle on the device: per-face
+// records in user order and one uniform grid per mesh whose cells list the faces
+// whose bounding boxes, widened by a margin, meet them.  Cells are 0.65 mean
+// edges wide: a smooth mesh's query then tests 6 faces instead of 11 with one
+// edge and 18 with 1.5 (131,072 rays on 327,680 faces: 1.52, 2.11 and 3.65 ms;
+// finer ones cost more than they save where steps leave the surface: on a rough
+// mesh 8.7 ms with one edge, 9.7 with 0.65, 11.0 with 0.5).  A mesh whose faces
+// differ so much in size that they meet kPiEntries cells each gets wider ones,
+// up to 1.5 edges.
+// Called with pi_mu held; on failure the caller frees what was allocated.
+constexpr uint64_t kPiEntries = 64;   // (a smooth mesh: 12)
+
+int build_pi(sg_mesh m) {
+    const sg::PackedMesh& pm = m->host;
+    const std::vector<int64_t>& fo = pm.face_off;
+    const int nm = (int)fo.size() - 1;
+    const sg::DevMesh M = m->dev();
+    // extents of each mesh, and the face records
+    std::vector<double> ext((size_t)nm * sg::kPiParts * sg::kPiExtent);
+    std::vector<sg::PiGrid> grid(nm);
     int rc = upload(&m->d_pigrid, grid, m->pi_bytes);
     if (rc != SG_OK) return rc;
     const size_t face_bytes = (size_t)m->n_faces * sizeof(sg::PiFace);
-    const size_t sum_at = ((total + 2 + (uint64_t)sg::scan_tiles((int64_t)total + 1)) * sizeof(uint32_t) + 7) & ~(size_t)7;
-    const size_t cell_bytes = sum_at + 8;
-    e = hipMalloc((void**)&m->d_piface, face_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&m->d_cell_start, cell_bytes);
+    const size_t off_bytes = (fo.size() * sizeof(int64_t) + 255) & ~(size_t)255;
+    void* tmp = nullptr;
+    hipError_t e = hipMalloc((void**)&m->d_piface, face_bytes);
+    if (e == hipSuccess) e = hipMalloc(&tmp, off_bytes + ext.size() * sizeof(double));
     if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
-    m->pi_bytes += face_bytes + cell_bytes;
-    uint32_t* cells = m->d_cell_start + 1;
-    auto* sum = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(m->d_cell_start) + sum_at);
-    uint64_t entries = 0;
-    e = sg::launch_pi_count(M, m->pi(), m->d_piface, cells, (int64_t)total, pad, cells + total + 1, sum, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(&entries, sum, sizeof entries, hipMemcpyDeviceToHost);
+    m->pi_bytes += face_bytes;
+    double* d_ext = reinterpret_cast<double*>(reinterpret_cast<char*>(tmp) + off_bytes);
+    e = hipMemcpy(tmp, fo.data(), fo.size() * sizeof(int64_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = sg::launch_pi_extents(M, reinterpret_cast<const int64_t*>(tmp), nm, d_ext, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = sg::launch_pi_faces(M, m->d_piface, nullptr);
+    // the grids
+    uint64_t total = 0, entries = 0;
+    double pad = 0.0;
+    for (const double edges : {0.65, 1.0, 1.5}) {
+        const bool last = edges == 1.5;
+        double scale;
+        total = pi_grids(fo, ext, edges, edges < 1.0 ? 128 : 32, grid, scale);
+        if (total >= ((uint64_t)1 << 31)) continue;
+        // distances within 1e-12 of the largest coordinate are one nearest point (float64 rounding);
+        // the cell search reaches 1e-9 further, past any rounding of a box distance
+        m->pi_tie = 1e-12 * scale;
+        m->pi_slack = 1e-9 * scale;
+        pad = scale * std::ldexp(1.0, -20);
+        auto* sum = reinterpret_cast<unsigned long long*>(tmp);
+        if (e == hipSuccess) e = hipMemcpy(m->d_pigrid, grid.data(), grid.size() * sizeof(sg::PiGrid), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(), sum, pad, nullptr);
+        if (e == hipSuccess) e = hipMemcpy(&entries, sum, sizeof entries, hipMemcpyDeviceToHost);
+        if (e != hipSuccess || last || entries <= kPiEntries * (uint64_t)m->n_faces) break;
+    }
+    (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "projection grid");
-    if (entries >= ((uint64_t)1 << 32) - 1) return fail(SG_E_OOM, "projection grid too large");
-    e = hipMalloc((void**)&m->d_cell_face, std::max<uint64_t>(entries, 1) * sizeof(int32_t));
+    if (total >= ((uint64_t)1 << 31) || entries >= ((uint64_t)1 << 32) - 1) return fail(SG_E_OOM, "projection grid too large");
+    const size_t cell_bytes = (total + 2 + (uint64_t)sg::scan_tiles((int64_t)total + 1)) * sizeof(uint32_t);
+    e = hipMalloc((void**)&m->d_cell_start, cell_bytes);
+    if (e == hipSuccess) e = hipMalloc((void**)&m->d_cell_face, std::max<uint64_t>(entries, 1) * sizeof(int32_t));
     if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
-    m->pi_bytes += (size_t)entries * sizeof(int32_t);
-    e = sg::launch_pi_fill(m->pi(), cells, m->d_cell_face, pad, nullptr);
+    m->pi_bytes += cell_bytes + (size_t)entries * sizeof(int32_t);
+    uint32_t* cells = m->d_cell_start + 1;
+    e = sg::launch_pi_count(m->pi(), cells, (int64_t)total, pad, cells + total + 1, nullptr);
+    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(), cells, m->d_cell_face, pad, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // later calls read it on any stream
     if (e != hipSuccess) return hip_fail(e, "projection grid");
     return SG_OK;

@@ -171,16 +171,18 @@ inline bool pi_ordered(int64_t rows, int64_t n_faces) {
 }
 size_t pi_order_workspace(int64_t n);
 hipError_t launch_pi_exp(const PiMesh& P, const DevMesh& M, const PiArgs& a, void* ws, hipStream_t s);
-// The projection data of a handle, in three parts.  Extents: kPiParts partial
+// The projection data of a handle, in five parts.  Extents: kPiParts partial
 // results per mesh (lowest and highest coordinates, sum of edge lengths, largest
-// absolute coordinate of a share of all vertices).  Faces and counts: the face
-// records, and at cells[c] the entries before cell c (cells[total]: all of
-// them; tile: scan_tiles(total + 1) words; sum: their number in 64 bits).  Fill: the entries; cells[c] moves
-// to the end of cell c, so that cells - 1 (a zero word) are the cells' starts.
+// absolute coordinate of a share of all vertices).  The face records.  The
+// number of cell entries that a choice of grids takes.  Counts: at cells[c] the
+// entries before cell c (cells[total]: all of them; tile: scan_tiles(total + 1)
+// words).  Fill: the entries; cells[c] moves to the end of cell c, so that
+// cells - 1 (a zero word) are the cells' starts.
 constexpr int kPiParts = 16, kPiExtent = 8;
 hipError_t launch_pi_extents(const DevMesh& M, const int64_t* face_off, int n_meshes, double* out, hipStream_t s);
-hipError_t launch_pi_count(const DevMesh& M, const PiMesh& P, PiFace* face, uint32_t* cells, int64_t total, double pad,
-                           uint32_t* tile, unsigned long long* sum, hipStream_t s);
+hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, hipStream_t s);
+hipError_t launch_pi_entries(const PiMesh& P, unsigned long long* sum, double pad, hipStream_t s);
+hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, double pad, uint32_t* tile, hipStream_t s);
 hipError_t launch_pi_fill(const PiMesh& P, uint32_t* cells, int32_t* cell_face, double pad, hipStream_t s);
 // EP (saved f', v') or GFD (seven PI walks per query, stacked in two launches).
 size_t pi_bwd_workspace(int64_t n, int32_t mode);

@@ -123,15 +123,15 @@ __device__ __forceinline__ int cell_of(double x, float o, float h, int n) {
     return min(max((int)floor(t), 0), n - 1);
 }
 
-// Visits every face listed in a cell whose box lies within R of q, rings of
-// cells outward from q's (clamped) cell.  `visit(face, R)` may shrink R.
+// Calls cell(ix, iy, iz) for every cell whose box lies within R of q, rings of
+// cells outward from q's (clamped) cell, from ring r0.  `cell` may shrink R.
 // Every cell of ring r >= 2 is at least (r - 1) h from q, which ends the
 // search once that exceeds R.
-template <class Visit>
-__device__ __forceinline__ void grid_visit(const PiMesh& P, const PiGrid& G, D3 q, double& R, Visit&& visit) {
+template <class Cell>
+__device__ __forceinline__ void grid_cells(const PiGrid& G, D3 q, const double& R, int r0, Cell&& cell) {
     const int cx = cell_of(q.x, G.ox, G.h, G.nx), cy = cell_of(q.y, G.oy, G.h, G.ny), cz = cell_of(q.z, G.oz, G.h, G.nz);
     const int maxr = max(G.nx, max(G.ny, G.nz));
-    for (int r = 0; r <= maxr; ++r) {
+    for (int r = r0; r <= maxr; ++r) {
         if (r >= 2 && (double)(r - 1) * (double)G.h * 0.999 > R) break;
         for (int dz = -r; dz <= r; ++dz) {
             const int iz = cz + dz;
@@ -145,13 +145,21 @@ __device__ __forceinline__ void grid_visit(const PiMesh& P, const PiGrid& G, D3 
                     const int ix = cx + dx;
                     if (ix < 0 || ix >= G.nx) continue;
                     if (box_dist2(G, q, ix, iy, iz) > R * R) continue;
-                    const uint32_t cell = G.cell0 + (uint32_t)((iz * G.ny + iy) * G.nx + ix);
-                    const uint32_t j1 = P.cell_start[cell + 1];
-                    for (uint32_t j = P.cell_start[cell]; j < j1; ++j) visit(P.cell_face[j], R);
+                    cell(ix, iy, iz);
                 }
             }
         }
     }
+}
+
+// Visits every face listed in these cells.  `visit(face, R)` may shrink R.
+template <class Visit>
+__device__ __forceinline__ void grid_visit(const PiMesh& P, const PiGrid& G, D3 q, double& R, Visit&& visit) {
+    grid_cells(G, q, R, 0, [&](int ix, int iy, int iz) {
+        const uint32_t cell = G.cell0 + (uint32_t)((iz * G.ny + iy) * G.nx + ix);
+        const uint32_t j1 = P.cell_start[cell + 1];
+        for (uint32_t j = P.cell_start[cell]; j < j1; ++j) visit(P.cell_face[j], R);
+    });
 }
 
 // The nearest point of the ray's mesh to q (project_to_mesh).  Faces within
@@ -230,8 +238,11 @@ __device__ __forceinline__ double face_dist2(D3 x0, D3 x1, D3 x2, D3 q) {
 // of cand: those whose squared distance is within 2^-20 of the smallest plus
 // pad, which covers 16 ties and the errors of face_dist2 at any distance
 // ((d + m)^2 <= d^2 (1 + 2^-20) + m^2 (1 + 2^20)).  Returns their number, or
-// -1 when the search has to be the general one: the cell of q holds no face,
-// the nearest is several cells away, or more than kPiCand faces tie.
+// -1 when more than kPiCand faces tie and the search has to be the general one.
+// Where the cell of q does not settle it, the rings of cells around it follow
+// (grid_cells): with the general search there instead, 131,072 rays on 327,680
+// faces in steps of 0.1 (ten edges) took 19.6 ms, now 5.0, and on a rough mesh
+// of 81,920 faces in steps of 0.03 35.8, now 10.4.
 constexpr int kPiCand = 8;
 constexpr int kPiAhead = 4;   // 1,000 rays on 327,680 faces: 1.63 ms with one record in flight, 1.01 with four
 constexpr int kPiBlock = 256;
@@ -262,6 +273,9 @@ __device__ __forceinline__ int near_faces(const PiMesh& P, const PiGrid& G, D3 q
                         cnt = 0;
                         over = false;
                     }
+                    bool listed = false;   // (a face is in every cell that it comes near)
+                    for (int i = 0; i < cnt; ++i) listed |= cand[i][t] == fid[k];
+                    if (listed) continue;
                     if (cnt < kPiCand) cand[cnt++][t] = fid[k];
                     else over = true;
                     best = fmin(best, d2);
@@ -270,32 +284,28 @@ __device__ __forceinline__ int near_faces(const PiMesh& P, const PiGrid& G, D3 q
         }
     };
     cell(cx, cy, cz);
-    if (!(best < __builtin_inf())) return -1;
+    auto radius = [&]() { return sqrt(best) * grow + m + P.slack; };
     // the cell lists the faces within kPiCover h of it: enough while the ball of the
     // best distance stays inside that (steps are short against the cells)
-    const double R = sqrt(best) * grow + m + P.slack;
+    double R = radius();
     const double lx = fma((double)cx, h, (double)G.ox), ly = fma((double)cy, h, (double)G.oy),
                  lz = fma((double)cz, h, (double)G.oz);
     const double reach = R - 0.999 * kPiCover * h;
     if (q.x - lx < reach || lx + h - q.x < reach || q.y - ly < reach || ly + h - q.y < reach || q.z - lz < reach ||
-        lz + h - q.z < reach) {
-        if (R > h) return -1;
-        const int x0 = cell_of(q.x - R, G.ox, G.h, G.nx), x1 = cell_of(q.x + R, G.ox, G.h, G.nx);
-        const int y0 = cell_of(q.y - R, G.oy, G.h, G.ny), y1 = cell_of(q.y + R, G.oy, G.h, G.ny);
-        const int z0 = cell_of(q.z - R, G.oz, G.h, G.nz), z1 = cell_of(q.z + R, G.oz, G.h, G.nz);
-        for (int iz = z0; iz <= z1; ++iz)
-            for (int iy = y0; iy <= y1; ++iy)
-                for (int ix = x0; ix <= x1; ++ix)
-                    if (ix != cx || iy != cy || iz != cz) cell(ix, iy, iz);
-    }
-    return over ? -1 : cnt;
+        lz + h - q.z < reach)
+        grid_cells(G, q, R, 1, [&](int ix, int iy, int iz) {
+            cell(ix, iy, iz);
+            R = radius();
+        });
+    return over || cnt == 0 ? -1 : cnt;
 }
 
 // project_to_mesh for a query near the surface.  Bound by float64 issue (about
-// 140 slots per face tested, 11 to 16 faces per step) with 131,072 rays, two
-// waves per SIMD.  Two full visits of the grid with face_closest, 27 cell boxes
-// tested in each, took 11.7 ms for these on 327,680 faces; with the candidates
-// 3.51 ms, and 2.73 ms with cells of one edge.
+// 140 slots per face tested, half of all cycles) and by the L1's accesses (three
+// loads per face) with 131,072 rays, two waves per SIMD.  Two full visits of the
+// grid with face_closest, 27 cell boxes tested in each, took 11.7 ms for these
+// on 327,680 faces; with the candidates 3.51 ms, with cells of one edge 2.73,
+// in a spatial order 2.10, with cells of 0.65 edges 1.52.
 __device__ __forceinline__ PiHit project_near(const PiMesh& P, const PiGrid& G, D3 q, int32_t (*cand)[kPiBlock]) {
     const int cnt = near_faces(P, G, q, cand);
     if (cnt < 0) return project_grid(P, G, q);
@@ -628,21 +638,25 @@ __global__ __launch_bounds__(256) void k_pi_faces(DevMesh M, PiFace* face) {
 }
 #pragma clang fp contract(on)
 
-// Adds face u to every cell its bounding box, widened by kPiCover h + pad, meets.
-template <class Add>
-__device__ __forceinline__ void face_cells(const PiMesh& P, int64_t u, double pad, Add&& add) {
+// The cells that face u's bounding box, widened by kPiCover h + pad, meets: i0 to i1 along each axis.
+__device__ __forceinline__ void face_box(const PiMesh& P, const PiGrid& G, int64_t u, double pad, int (&i0)[3], int (&i1)[3]) {
     const PiFace& F = P.face[u];
-    const PiGrid G = P.grid[mesh_of(P, (int32_t)u)];
     const double marg = kPiCover * (double)G.h + pad;
     const float o[3] = {G.ox, G.oy, G.oz};
     const int n[3] = {G.nx, G.ny, G.nz};
-    int i0[3], i1[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const double a = fmin(fmin(F.x0[c], F.x1[c]), F.x2[c]), b = fmax(fmax(F.x0[c], F.x1[c]), F.x2[c]);
         i0[c] = cell_of(a - marg, o[c], G.h, n[c]);
         i1[c] = cell_of(b + marg, o[c], G.h, n[c]);
     }
+}
+
+template <class Add>
+__device__ __forceinline__ void face_cells(const PiMesh& P, int64_t u, double pad, Add&& add) {
+    const PiGrid G = P.grid[mesh_of(P, (int32_t)u)];
+    int i0[3], i1[3];
+    face_box(P, G, u, pad, i0, i1);
     for (int iz = i0[2]; iz <= i1[2]; ++iz)
         for (int iy = i0[1]; iy <= i1[1]; ++iy)
             for (int ix = i0[0]; ix <= i1[0]; ++ix) add(G.cell0 + (uint32_t)((iz * G.ny + iy) * G.nx + ix));
@@ -652,17 +666,23 @@ __global__ __launch_bounds__(256) void k_pi_zero(uint32_t* x, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) x[i] = 0u;
 }
 
-// (sum: all entries in 64 bits, since the counts wrap where a few faces meet very many cells)
-__global__ __launch_bounds__(256) void k_pi_count(PiMesh P, uint32_t* cells, unsigned long long* sum, double pad) {
+// All faces' cells, added up in 64 bits without visiting them (a few large faces can meet very many).
+__global__ __launch_bounds__(256) void k_pi_entries(PiMesh P, unsigned long long* sum, double pad) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     unsigned long long n = 0ull;
-    if (u < P.n_faces)
-        face_cells(P, u, pad, [&](uint32_t c) {
-            atomicAdd(cells + c, 1u);
-            ++n;
-        });
+    if (u < P.n_faces) {
+        int i0[3], i1[3];
+        face_box(P, P.grid[mesh_of(P, (int32_t)u)], u, pad, i0, i1);
+        n = 1ull;
+        for (int c = 0; c < 3; ++c) n *= (unsigned long long)(i1[c] - i0[c] + 1);
+    }
     for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
     if ((threadIdx.x & 63u) == 0u) atomicAdd(sum, n);
+}
+
+__global__ __launch_bounds__(256) void k_pi_count(PiMesh P, uint32_t* cells, double pad) {
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u < P.n_faces) face_cells(P, u, pad, [&](uint32_t c) { atomicAdd(cells + c, 1u); });
 }
 
 __global__ __launch_bounds__(256) void k_pi_fill(PiMesh P, uint32_t* cells, int32_t* cell_face, double pad) {
@@ -920,14 +940,21 @@ hipError_t launch_pi_extents(const DevMesh& M, const int64_t* face_off, int n_me
     return hipGetLastError();
 }
 
-hipError_t launch_pi_count(const DevMesh& M, const PiMesh& P, PiFace* face, uint32_t* cells, int64_t total, double pad,
-                           uint32_t* tile, unsigned long long* sum, hipStream_t s) {
-    const dim3 grid((unsigned)((M.n_faces + 255) / 256)), block(256);
-    hipLaunchKernelGGL(k_pi_faces, grid, block, 0, s, M, face);
-    hipLaunchKernelGGL(k_pi_zero, dim3((unsigned)std::min<int64_t>((total + 256) / 256, 8192)), block, 0, s, cells - 1,
+hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, hipStream_t s) {
+    hipLaunchKernelGGL(k_pi_faces, dim3((unsigned)((M.n_faces + 255) / 256)), dim3(256), 0, s, M, face);
+    return hipGetLastError();
+}
+
+hipError_t launch_pi_entries(const PiMesh& P, unsigned long long* sum, double pad, hipStream_t s) {
+    hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(sum), (int64_t)2);
+    hipLaunchKernelGGL(k_pi_entries, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, sum, pad);
+    return hipGetLastError();
+}
+
+hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, double pad, uint32_t* tile, hipStream_t s) {
+    hipLaunchKernelGGL(k_pi_zero, dim3((unsigned)std::min<int64_t>((total + 256) / 256, 8192)), dim3(256), 0, s, cells - 1,
                        total + 2);
-    hipLaunchKernelGGL(k_pi_zero, dim3(1), block, 0, s, reinterpret_cast<uint32_t*>(sum), (int64_t)2);
-    hipLaunchKernelGGL(k_pi_count, grid, block, 0, s, P, cells, sum, pad);
+    hipLaunchKernelGGL(k_pi_count, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, cells, pad);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? launch_scan(cells, total + 1, tile, s) : e;
 }

@@ -5,7 +5,9 @@ both take the exact distances and the same tie rule.
   * more faces tying at a vertex than the candidate list holds (the apex of a
     cone of 24 faces, reached from outside its corner);
   * queries several cells away from the surface (steps of the length of v);
-  * queries whose nearest face lies outside their cell's list (coarse steps);
+  * queries whose nearest face lies outside their cell's list (coarse steps, a
+    rough surface), so that several rings of cells list the same faces;
+  * faces so unequal in size that they would fill too many cells;
   * batches large enough to be reordered, on a mesh beyond one L2.
 """
 import numpy as np
@@ -38,7 +40,19 @@ def _double_cone(sides=24):
     return M.canonical(X, F)
 
 
+def _rough():
+    X, F = M.canonical(*M.icosphere(4))
+    g = np.random.default_rng(41)
+    return (X * (1.0 + 0.02 * g.standard_normal((X.shape[0], 1)))).astype(np.float32), F
+
+
+def _unequal():   # 5,120 faces of a hundredth of the tetrahedron's size, and the tetrahedron
+    (X, F), (Y, G) = M.icosphere(4), M.tetrahedron()
+    return M.canonical(np.concatenate([0.01 * X + 2.0, Y]), np.concatenate([F, G + X.shape[0]]))
+
+
 @pytest.mark.parametrize("kind,step,length", [
+    ("rough", 0.02, 0.5), ("rough", 0.2, 2.0), ("unequal", 0.002, 0.05), ("unequal", 0.3, 2.0),
     ("cone", 0.05, 1.0), ("cone", 0.3, 2.0),
     ("tetrahedron", 1.0, 6.0), ("sphere", 1.0, 3.0),
     ("sphere", 0.1, 2.0), ("torus", 0.25, 1.5)])
@@ -47,6 +61,7 @@ def test_search_equals_scan(kind, step, length):
     g = np.random.default_rng(17)
     X, F = {"cone": _double_cone, "tetrahedron": lambda: M.canonical(*M.tetrahedron()),
             "sphere": lambda: M.canonical(*M.icosphere(3)),
+            "rough": _rough, "unequal": _unequal,
             "torus": lambda: M.canonical(*M.torus_grid(30, 10, 0.2, g))}[kind]()
     r = random_rays(X, F, 2049, g, uniform_len(0.0, length), K=1)
     if kind == "cone":   # toward the apex of the start face, so that the steps pass it

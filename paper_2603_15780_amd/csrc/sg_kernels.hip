@@ -867,7 +867,7 @@ SG_HD __forceinline__ void find_exit(const FaceWords& q, const Ray& st, float sn
 // Crosses the exit edge into the next chart (transport_over_edge): the crossed
 // edge keeps its points and angles; the remaining length is compensated.
 template <bool kHash, bool kFlip>
-SG_HD __forceinline__ void cross_edge(const DevMesh& M, const Exit& x, float len, int32_t nx, Ray& st) {
+SG_HD __forceinline__ void cross_edge(const Exit& x, float len, int32_t nx, uint32_t id, Ray& st) {
     const bool via_ca = lane_of(x.mca);
     const float dm = x.mu * len, dom = x.omu * len;
     uint32_t ph = st.phi + x.turn;
@@ -888,7 +888,7 @@ SG_HD __forceinline__ void cross_edge(const DevMesh& M, const Exit& x, float len
     st.h = kFlip ? nb_he(nx) : nx;
     st.bias = 0.f;
     st.ncross += 1;
-    if (kHash) st.hash = fnv_face(st.hash, (uint32_t)M.order[he_face(st.h)]);
+    if (kHash) st.hash = fnv_face(st.hash, id);
 }
 
 // A step that reaches the cap, a vertex or the boundary, from its start (the
@@ -945,7 +945,7 @@ SG_HD __forceinline__ int odd_step(const DevMesh& M, Ray& st, int32_t max_steps,
         return kStepDone;
     }
     // a vertex passed too far away to snap: an ordinary crossing
-    cross_edge<kHash, kFlip>(M, x, via_ca ? r.lac : r.lbc, nx, st);
+    cross_edge<kHash, kFlip>(x, via_ca ? r.lac : r.lbc, nx, kHash ? (uint32_t)M.order[he_face(nb_he(nx))] : 0u, st);
     return kStepContinue;
 }
 
@@ -991,6 +991,7 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("" : "+v"(len), "+v"(x.turn));   // picked here: the new record takes the old one's registers
 #endif
+    const uint32_t id = kHash ? (uint32_t)M.order[he_face(max(nx, 0))] : 0u;
     q = face_words(face_rec(M, max(nx, 0)));   // (no neighbour: any face)
     const float Lr = st.Lhi + st.Llo;
     const uint64_t live = lane_mask(alive);
@@ -998,7 +999,7 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int
     const uint64_t m_odd = (lane_mask(st.ncross >= max_steps) | lane_mask(x.mu < snap) | lane_mask(x.omu < snap) |
                             lane_mask(nx < 0)) & ~m_end & live;
     if (lane_of(live & ~(m_end | m_odd)))
-        cross_edge<kHash, kFlip>(M, x, len, nx, st);
+        cross_edge<kHash, kFlip>(x, len, nx, id, st);
     int ev = kStepContinue;
     if (lane_of(m_end)) {
         set_final(fin, st, fmaf(Lr, cs, st.s), Lr * sn, kRayOk);
@@ -1018,23 +1019,20 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int
 // With hole avoidance an odd step is common (a ray that meets a hole slides and
 // looks through vertex fans, some 4 us of dependent loads) and one lane's would
 // hold up its whole wave.  Such a lane is parked instead, and the wave takes the
-// parked lanes together once there are kParkMin of them or no other lane can
-// walk on.  200,003 rays on 94,000 faces with holes: 0.95 ms taken at once, 0.47,
-// 0.40, 0.43 and 0.49 ms with 8, 16, 32 and 64 lanes.
+// parked lanes together once there are kParkMin of them, the first has waited
+// kParkWait steps, or no other lane can walk on.  200,003 rays on 94,000 faces
+// with holes: 0.95 ms taken at once, 0.47, 0.40, 0.43 and 0.49 ms with 8, 16, 32
+// and 64 lanes.  Where odd steps are rare (a vertex now and then, one hole) a lane
+// that waits for the others to be parked too ends long after them: 300,000 rays
+// on 327,680 faces, one left out, take 517 us without a bound on the wait, 422,
+// 420, 430 and 452 with 32, 48, 64 and 128 steps, 415 if taken at once; those
+// with holes 0.42, 0.40, 0.39 and 0.39 ms.
 constexpr int kParkMin = 16;
+constexpr int kParkWait = 48;
 
-template <bool kHash, bool kFlip, bool kHole>
-SG_HD __forceinline__ int take_parked(const DevMesh& M, uint64_t act, uint64_t& park, int ev, FaceWords& q, Ray& st,
-                                      int32_t max_steps, float snap, Final& fin) {
-    park |= lane_mask(ev == kStepOdd);
-    if (park != 0ull && (__builtin_popcountll(park) >= kParkMin || (act & ~park) == 0ull)) {
-        if (lane_of(park)) {
-            ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
-            if (ev == kStepContinue) q = face_words(face_rec(M, st.h));
-        }
-        park = 0ull;
-    }
-    return ev;
+SG_HD __forceinline__ bool park_full(uint64_t act, uint64_t park, int& waited) {
+    waited = park != 0ull ? waited + 1 : 0;
+    return park != 0ull && (__builtin_popcountll(park) >= kParkMin || waited >= kParkWait || (act & ~park) == 0ull);
 }
 
 template <bool kHash, bool kFlip, bool kHole>
@@ -1042,11 +1040,23 @@ SG_HD __forceinline__ void walk_to_end(const DevMesh& M, Ray& st, int32_t max_st
     FaceWords q = face_words(face_rec(M, st.h));
     if constexpr (kHole) {   // (the lanes that are here, as one wave)
         uint64_t act = lane_mask(true), park = 0ull;
+        int waited = 0;
         while (act != 0ull) {
-            int ev = kStepContinue;
-            if (lane_of(act & ~park)) ev = walk_step<kHash, kFlip, true, false, true>(M, q, st, max_steps, snap, fin);
-            ev = take_parked<kHash, kFlip, true>(M, act, park, ev, q, st, max_steps, snap, fin);
-            act &= ~lane_mask(ev == kStepDone);
+            bool odd = false, done = false;
+            if (lane_of(act & ~park)) {
+                const int ev = walk_step<kHash, kFlip, true, false, true>(M, q, st, max_steps, snap, fin);
+                odd = ev == kStepOdd;
+                done = ev == kStepDone;
+            }
+            park |= lane_mask(odd);
+            if (park_full(act, park, waited)) {
+                if (lane_of(park)) {
+                    done = odd_step<kHash, kFlip, true>(M, st, max_steps, snap, fin) == kStepDone;
+                    if (!done) q = face_words(face_rec(M, st.h));
+                }
+                park = 0ull;
+            }
+            act &= ~lane_mask(done);
         }
     } else {
         while (walk_step<kHash, kFlip, false>(M, q, st, max_steps, snap, fin) == kStepContinue) {
@@ -1817,7 +1827,8 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
     int used = kBins ? 0 : kGxChunk;
     bool spill = kBins ? false : sink.rec == nullptr;
     uint64_t act = 0ull;    // lanes with a ray in flight
-    uint64_t park = 0ull;   // of these, with an odd step to take (take_parked)
+    int waited = 0;         // steps since the first was parked
+    uint64_t park = 0ull;   // of these, with an odd step to take (kParkMin)
     QueueCursor qc = queue_start(nq);
     int64_t q = 0;
     int32_t ray = 0;   // with fin_out: the query index, carried in the initial state's crossing count
@@ -1874,12 +1885,23 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
                 }
             };
             if constexpr (kHole) {
-                Final fin;
-                int ev = -1;   // (a lane without a ray, or parked)
-                if (lane_of(act & ~park))
-                    ev = walk_step<kHash, kFlip, true, kGX, true>(M, wq, st, max_steps, snap, fin, true, gsn, gcs);
-                ev = take_parked<kHash, kFlip, true>(M, act, park, ev, wq, st, max_steps, snap, fin);
-                if (ev == kStepDone || ev == kStepContinue) settle(ev, fin);
+                bool odd = false;
+                if (lane_of(act & ~park)) {
+                    Final fin;
+                    const int ev = walk_step<kHash, kFlip, true, kGX, true>(M, wq, st, max_steps, snap, fin, true, gsn, gcs);
+                    odd = ev == kStepOdd;
+                    if (!odd) settle(ev, fin);
+                }
+                park |= lane_mask(odd);
+                if (park_full(act, park, waited)) {
+                    if (lane_of(park)) {
+                        Final fin;
+                        const int ev = odd_step<kHash, kFlip, true>(M, st, max_steps, snap, fin);
+                        if (ev == kStepContinue) wq = face_words(face_rec(M, st.h));
+                        settle(ev, fin);
+                    }
+                    park = 0ull;
+                }
             } else if (lane_of(act)) {
                 Final fin;
                 const int ev = walk_step<kHash, kFlip, false, kGX>(M, wq, st, max_steps, snap, fin, true, gsn, gcs);

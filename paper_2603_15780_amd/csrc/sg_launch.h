@@ -164,10 +164,12 @@ struct PiArgsT {
 using PiArgs = PiArgsT<float>;
 // ws: pi_order_workspace(n) bytes for a spatial order of the rays, or null (as
 // they come).  The order pays once the face records exceed one L2 (4 MB) and
-// there are enough rays for more than half a wave per SIMD (below, a step waits for its own
-// loads): 131,072 rays on 20,480 faces take 1.60 ms ordered, 1.56 not.
+// there are rays for a wave per SIMD (below, a step waits for its own loads):
+// 131,072 rays on 20,480 faces take 1.14 ms ordered, 1.07 not, on 327,680 faces
+// 1.51 and 1.96; 65,536 rays on 81,920 faces 0.81 and 0.85, on 1,310,720 1.11 and
+// 1.14; 40,000 rays there 1.06 and 1.03.
 inline bool pi_ordered(int64_t rows, int64_t n_faces) {
-    return rows >= 32768 && n_faces * (int64_t)sizeof(PiFace) >= ((int64_t)4 << 20);
+    return rows >= 65536 && n_faces * (int64_t)sizeof(PiFace) >= ((int64_t)4 << 20);
 }
 size_t pi_order_workspace(int64_t n);
 hipError_t launch_pi_exp(const PiMesh& P, const DevMesh& M, const PiArgs& a, void* ws, hipStream_t s);

@@ -693,8 +693,8 @@ __global__ __launch_bounds__(256) void k_pi_fill(PiMesh P, uint32_t* cells, int3
 // The grid search's ray order: rays by start face, kPiBuckets stretches of the
 // spatial face order, so that the rays an XCD has in flight search the same
 // cells.  Without it they fetch face records and cell lists from the whole mesh,
-// a third of which missed the L2: 131,072 rays on 327,680 faces 2.73 -> 2.10 ms,
-// 1,048,576 rays 21.6 -> 13.7 ms.
+// a third of which missed the L2: 131,072 rays on 327,680 faces 1.96 -> 1.51 ms,
+// 1,048,576 rays 15.4 -> 9.8 ms.
 constexpr int kPiBuckets = 8192;
 
 __device__ __forceinline__ int pi_bucket(const DevMesh& M, int32_t fu) {

@@ -74,9 +74,9 @@ def test_search_equals_scan(kind, step, length):
           mesh.pi_exp(*t, step=step, want_steps=True, search=sg.PI_SCAN))
 
 
-@pytest.mark.parametrize("n", [32768, 40001])
+@pytest.mark.parametrize("n", [32768, 40001, 65536, 70001])
 def test_ordered_batch_equals_slices(n):
-    """81,920 faces: a batch from 32,768 rays on is reordered, its slices are not; the
+    """81,920 faces: a batch from 65,536 rays on is reordered, its slices are not; the
     backward's stacked launches are (3 n rows), and their gradients do not change."""
     from paper_2603_15780_amd import sg
     X, F = M.canonical(*M.icosphere(6))

@@ -170,6 +170,13 @@ void free_mesh(sg_mesh_s* m) {
     delete m;
 }
 
+// For a walk of one ray per lane whatever the options say: its threshold cannot
+// exceed the 64 rays of a wave, or the wave would wait for it for ever.
+void one_ray_per_lane(const sg_opts* in, sg_opts& o, int32_t refill) {
+    o.rays_per_lane = 1;
+    o.refill_min = in && in->refill_min > 0 ? std::min(o.refill_min, 64) : refill;
+}
+
 int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1) {
     sg_opts_default(&o);
     if (in) o = *in;
@@ -183,6 +190,7 @@ int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1
     if (o.rays_per_lane > 2) return fail(SG_E_ARG, "rays_per_lane must be 1 or 2");
     if (o.refill_min <= 0) o.refill_min = 48 * o.rays_per_lane;
     if (o.refill_min > 64 * o.rays_per_lane) return fail(SG_E_ARG, "refill_min must be at most 64 per ray slot");
+    if (o.kernel == SG_KERNEL_PARTITIONED) one_ray_per_lane(in, o, 48);
     if (o.boundary_mode != SG_BOUNDARY_STOP && o.boundary_mode != SG_BOUNDARY_AVOID)
         return fail(SG_E_ARG, "unknown boundary_mode %d", o.boundary_mode);
     if (o.ray_queues <= 0) o.ray_queues = 8;
@@ -246,7 +254,7 @@ hipError_t give_workspace(Workspace& w, hipStream_t st) {
 int check_bwd_opts(const sg_opts* in, sg_opts& o, sg_mesh m) {
     const int rc = check_opts(in, o, m);
     if (rc == SG_OK && o.kernel == SG_KERNEL_PARTITIONED) o.walk_blocks = m->cu_count * m->walk_blocks_per_cu;
-    if (rc == SG_OK && !(in && in->refill_min > 0)) o.refill_min = 32 * o.rays_per_lane;
+    if (rc == SG_OK) one_ray_per_lane(in, o, 32);
     return rc;
 }
 

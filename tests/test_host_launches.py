@@ -1,0 +1,59 @@
+"""What the library's host code launches, and what it makes of failures, on a
+stand-in HIP runtime (no GPU)."""
+import ctypes as C
+import os
+import shutil
+
+import numpy as np
+import pytest
+
+import fake_hip
+from paper_2603_15780_amd import build as B
+from paper_2603_15780_amd import sg
+from workloads import meshes as M
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if not os.path.exists(B.HIPCC) or not shutil.which("g++"):
+        pytest.skip("hipcc or g++ not available")
+    return fake_hip.Lib(fake_hip.build(str(tmp_path_factory.mktemp("host"))))
+
+
+def _int(args, k):
+    return C.cast(args[k], C.POINTER(C.c_int32)).contents.value
+
+
+def _canonical(kind):
+    return M.canonical(*(M.mobius_strip(40, 6) if kind == "mobius" else M.icosphere(3)))
+
+
+# the refill threshold's place among the arguments, and the rays a wave holds
+REFILL = {"k_walk": (6, 64), "k_walk2": (6, 128), "k_walk_bwd": (6, 64), "k_walk_gx": (6, 64),
+          "k_adjoint_walk": (6, 64), "k_walk_round": (8, 64)}
+
+
+@pytest.mark.parametrize("kind", ["icosphere", "mobius"])
+@pytest.mark.parametrize("refill", [0, 1, 64, 65, 96, 128])
+def test_refill_threshold_is_reached(lib, kind, refill):
+    """A wave refills, and leaves its loop, once this many of its rays have ended:
+    a threshold beyond the rays it holds would never be."""
+    X, F = _canonical(kind)
+    h, seen = lib.mesh(X, F), set()
+
+    def launch(name, dev, args):
+        if name in REFILL:
+            seen.add((name, _int(args, REFILL[name][0])))
+
+    gx, n, kw = fake_hip.arr(len(X), 3, dtype=np.float64), 1000, dict(rays_per_lane=2, refill_min=refill)
+    with lib.on_launch(launch):
+        for kernel in (sg.KERNEL_PERSISTENT, sg.KERNEL_PARTITIONED):
+            assert lib.exp(h, n, kernel=kernel, **kw) == 0
+            for mode in (sg.BWD_EP, sg.BWD_GFD):
+                for saved in (True, False):
+                    if saved or mode == sg.BWD_GFD or kind == "mobius":
+                        assert lib.backward(h, mode, n, saved=saved, kernel=kernel, **kw) == 0
+                assert lib.backward(h, mode, n, grad_X=gx, kernel=kernel, **kw) == 0
+        assert lib.backward(h, sg.BWD_EP, n, grad_X=gx, gradx_records=-1, **kw) == 0
+    assert {name for name, _ in seen} == set(REFILL) - {"k_walk"}
+    assert all(1 <= at <= REFILL[name][1] for name, at in seen), seen

@@ -3741,7 +3741,8 @@ hipError_t launch_backward(const DevMesh& M, const BwdArgs& a_in, void* ws, cons
                            P.gx_saved ? (const StateRec*)nullptr : (const StateRec*)s1, per1, s3, cvec, sterm, srank,
                            fstart);
         // each start face's queries as one list (counts to offsets, then the ranks place them)
-        (void)launch_scan(fstart, nfs, reinterpret_cast<uint32_t*>(base + L.ftile), s);
+        const hipError_t e = launch_scan(fstart, nfs, reinterpret_cast<uint32_t*>(base + L.ftile), s);
+        if (e != hipSuccess) return e;   // (any launch so far)
         hipLaunchKernelGGL(k_gradx_start_place, dim3((unsigned)grid), dim3(block), 0, s, M, a);
         hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, counter);
         const int64_t nh = 3 * M.n_faces;

@@ -724,17 +724,21 @@ __global__ __launch_bounds__(256) void k_pi_place(DevMesh M, int64_t n, const in
     if (i < n) order[cnt[pi_bucket(M, f[i])] + rank[i]] = (int32_t)i;
 }
 
-// order[n] | rank[n] | bucket counts | scan tiles; returns the order.
-const int32_t* pi_order(const DevMesh& M, int64_t n, const int32_t* f, void* ws, hipStream_t s) {
+// order[n] | rank[n] | bucket counts | scan tiles; out: the order.  An error here
+// or in an earlier launch is returned: the rays are not to be taken in an order
+// that was not written.
+hipError_t pi_order(const DevMesh& M, int64_t n, const int32_t* f, void* ws, const int32_t** out, hipStream_t s) {
     auto* order = reinterpret_cast<int32_t*>(ws);
     auto* rank = reinterpret_cast<uint32_t*>(order + n);
     uint32_t* cnt = rank + n;
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     hipLaunchKernelGGL(k_pi_zero, dim3(32), block, 0, s, cnt, (int64_t)kPiBuckets + 1);
     hipLaunchKernelGGL(k_pi_rank, grid, block, 0, s, M, n, f, cnt, rank);
-    (void)launch_scan(cnt, kPiBuckets + 1, cnt + kPiBuckets + 1, s);
+    const hipError_t e = launch_scan(cnt, kPiBuckets + 1, cnt + kPiBuckets + 1, s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_pi_place, grid, block, 0, s, M, n, f, (const uint32_t*)cnt, (const uint32_t*)rank, order);
-    return order;
+    *out = order;
+    return hipGetLastError();
 }
 
 template <class T>
@@ -943,8 +947,8 @@ size_t pi_order_workspace(int64_t n) {
 
 hipError_t launch_pi_exp(const PiMesh& P, const DevMesh& M, const PiArgs& a_in, void* ws, hipStream_t s) {
     PiArgs a = a_in;
-    if (ws) a.order = pi_order(M, a.n, a.f, ws, s);
-    return launch_pi(P, a, s);
+    const hipError_t e = ws ? pi_order(M, a.n, a.f, ws, &a.order, s) : hipSuccess;
+    return e == hipSuccess ? launch_pi(P, a, s) : e;
 }
 
 hipError_t launch_pi_extents(const DevMesh& M, const int64_t* face_off, int n_meshes, double* out, hipStream_t s) {
@@ -995,12 +999,12 @@ hipError_t launch_pi_backward(const PiMesh& P, const DevMesh& M, const BwdArgs& 
     const bool ordered = !pa.scan && pi_ordered(3 * n, M.n_faces) && pi_order_workspace(4 * n) <= stack_layout(3 * n).bytes &&
                          pi_order_workspace(3 * n) <= 24 * 3 * (size_t)n;
     PiArgsT<double> a1 = stack_args(pa, s1, 4 * n, 1), a2 = stack_args(pa, s2, 3 * n, 0);
-    if (ordered) a1.order = pi_order(M, a1.n, a1.f, base + stack_layout(4 * n).bytes, s);
-    hipError_t e = launch_pi(P, a1, s);
+    hipError_t e = ordered ? pi_order(M, a1.n, a1.f, base + stack_layout(4 * n).bytes, &a1.order, s) : hipSuccess;
+    if (e == hipSuccess) e = launch_pi(P, a1, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_pi_gfd_stage2, grid, block, 0, s, P, a, s1, s2);
-    if (ordered) a2.order = pi_order(M, a2.n, a2.f, s2.W, s);
-    e = launch_pi(P, a2, s);
+    if (ordered) e = pi_order(M, a2.n, a2.f, s2.W, &a2.order, s);
+    if (e == hipSuccess) e = launch_pi(P, a2, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_pi_gfd_assemble, grid, block, 0, s, P, a, s1, s2);
     return hipGetLastError();

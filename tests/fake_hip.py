@@ -82,3 +82,16 @@ class Lib:
         gv, gb = arr(n, 3), arr(n, 3)
         return self.L.sg_exp_backward(h, mode, n, ptr(f), ptr(b), ptr(v), ptr(fo), ptr(bo), ptr(vo), ptr(st), ptr(g),
                                       ptr(gv), ptr(gb), ptr(grad_X), C.byref(o), None)
+
+    def pi_exp(self, h, n, step=0.01, search=sg.PI_GRID):
+        f, b, v = arr(n, dtype=np.int32), arr(n, 3), arr(n, 3)
+        out = [arr(n, dtype=np.int32), arr(n, 3), arr(n, 3), arr(n, 3)]
+        po = sg.pi_opts(step, None, search)
+        return self.L.sg_pi_exp(h, n, ptr(f), ptr(b), ptr(v), 0, None, *[ptr(x) for x in out], None, None, None, C.byref(po),
+                                None)
+
+    def pi_backward(self, h, n, step=0.01):
+        f, b, v, g, gv, gb = arr(n, dtype=np.int32), *[arr(n, 3) for _ in range(5)]
+        po = sg.pi_opts(step)
+        return self.L.sg_pi_backward(h, sg.BWD_GFD, n, ptr(f), ptr(b), ptr(v), None, None, ptr(g), ptr(gv), ptr(gb),
+                                     C.byref(po), None, None)

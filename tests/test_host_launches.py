@@ -57,3 +57,61 @@ def test_refill_threshold_is_reached(lib, kind, refill):
         assert lib.backward(h, sg.BWD_EP, n, grad_X=gx, gradx_records=-1, **kw) == 0
     assert {name for name, _ in seen} == set(REFILL) - {"k_walk"}
     assert all(1 <= at <= REFILL[name][1] for name, at in seen), seen
+
+
+@pytest.fixture(scope="module")
+def big(lib):   # (81,920 faces: large batches of the projection map take their rays in order)
+    return lib.mesh(*M.canonical(*M.icosphere(6)))
+
+
+ERROR = 719   # hipErrorLaunchFailure
+
+
+@pytest.mark.parametrize("call", [
+    "exp_plain", "exp", "exp_partitioned", "ep_gradx", "ep_gradx_unsorted", "ep_gradx_walked", "gfd", "gfd_walked", "gfd_gradx",
+    "pi_exp", "pi_scan", "pi_ordered", "pi_backward", "pi_backward_ordered"])
+def test_a_failed_launch_is_reported(lib, big, call):
+    """Whichever launch of a call fails, the call returns the error, and the next one does not."""
+    gx = fake_hip.arr(40962, 3, dtype=np.float64)
+    run = {
+        "exp_plain": lambda: lib.exp(big, 100, kernel=sg.KERNEL_PLAIN),
+        "exp": lambda: lib.exp(big, 1000, kernel=sg.KERNEL_PERSISTENT),
+        "exp_partitioned": lambda: lib.exp(big, 1000, kernel=sg.KERNEL_PARTITIONED),
+        "ep_gradx": lambda: lib.backward(big, sg.BWD_EP, 1000, grad_X=gx),
+        "ep_gradx_unsorted": lambda: lib.backward(big, sg.BWD_EP, 1000, grad_X=gx, gradx_records=-1),
+        "ep_gradx_walked": lambda: lib.backward(big, sg.BWD_EP, 1000, grad_X=gx, boundary_mode=1),
+        "gfd": lambda: lib.backward(big, sg.BWD_GFD, 1000),
+        "gfd_walked": lambda: lib.backward(big, sg.BWD_GFD, 1000, saved=False),
+        "gfd_gradx": lambda: lib.backward(big, sg.BWD_GFD, 1000, grad_X=gx),
+        "pi_exp": lambda: lib.pi_exp(big, 1000),
+        "pi_scan": lambda: lib.pi_exp(big, 1000, search=sg.PI_SCAN),
+        "pi_ordered": lambda: lib.pi_exp(big, 70000),
+        "pi_backward": lambda: lib.pi_backward(big, 1000),
+        "pi_backward_ordered": lambda: lib.pi_backward(big, 30000),
+    }[call]
+    launched = []
+    with lib.on_launch(lambda name, dev, args: launched.append(name)):
+        assert run() == 0   # (the projection's first call builds its grid)
+        launched.clear()
+        assert run() == 0
+    total, kept = len(launched), []
+    for j in range(total):
+        count = iter(range(10 ** 6))
+        with lib.on_launch(lambda name, dev, args: ERROR if next(count) == j else 0):
+            rc = run()
+        if rc != sg.SG_E_HIP:
+            kept.append((j, launched[j], rc))
+        assert run() == 0
+    assert total >= 1 and not kept, kept
+
+
+def test_a_failed_grid_build_is_reported_and_tried_again(lib):
+    h = lib.mesh(*_canonical("icosphere"))
+    launched = []
+    with lib.on_launch(lambda name, dev, args: launched.append(name)):
+        assert lib.pi_exp(lib.mesh(*_canonical("icosphere")), 100) == 0
+    for j in range(len(launched)):
+        count = iter(range(10 ** 6))
+        with lib.on_launch(lambda name, dev, args: ERROR if next(count) == j else 0):
+            assert lib.pi_exp(h, 100) == sg.SG_E_HIP, launched[j]
+    assert lib.pi_exp(h, 100) == 0

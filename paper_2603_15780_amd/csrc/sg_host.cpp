@@ -125,6 +125,26 @@ struct DSU {
     }
 };
 
+// The mesh's device is current while this lives: for what the library runs on the
+// mesh's own data (new positions, the projection grid), whichever device the
+// caller has current.
+struct OnDevice {
+    int was = -1;
+    hipError_t err = hipSuccess;
+    explicit OnDevice(int device) {
+        int cur = device;
+        err = hipGetDevice(&cur);
+        if (err != hipSuccess || cur == device) return;
+        err = hipSetDevice(device);
+        if (err == hipSuccess) was = cur;
+    }
+    ~OnDevice() {
+        if (was >= 0) (void)hipSetDevice(was);
+    }
+    OnDevice(const OnDevice&) = delete;
+    OnDevice& operator=(const OnDevice&) = delete;
+};
+
 template <class T>
 int upload(T** dptr, const std::vector<T>& h, size_t& bytes) {
     const size_t nb = h.size() * sizeof(T);
@@ -400,6 +420,8 @@ int build_pi(sg_mesh m) {
 int ensure_pi(sg_mesh m) {
     std::lock_guard<std::mutex> lock(m->pi_mu);
     if (m->pi_ready) return SG_OK;
+    const OnDevice dev(m->device);
+    if (dev.err != hipSuccess) return hip_fail(dev.err, "projection grid");
     int rc;
     try {
         rc = build_pi(m);
@@ -818,6 +840,8 @@ int sg_mesh_update_vertices(sg_mesh mesh, const float* X_host, int64_t n_verts) 
     if (!X_host) return fail(SG_E_ARG, "X_host is NULL");
     if (n_verts != mesh->n_verts)
         return fail(SG_E_ARG, "n_verts %lld does not match the mesh's %lld", (long long)n_verts, (long long)mesh->n_verts);
+    const OnDevice dev(mesh->device);
+    if (dev.err != hipSuccess) return hip_fail(dev.err, "vertex update");
     const size_t need = sg::pos_workspace(n_verts, mesh->n_faces);
     hipError_t e = hipSuccess;
     if (!mesh->d_pos) {

@@ -115,3 +115,22 @@ def test_a_failed_grid_build_is_reported_and_tried_again(lib):
         with lib.on_launch(lambda name, dev, args: ERROR if next(count) == j else 0):
             assert lib.pi_exp(h, 100) == sg.SG_E_HIP, launched[j]
     assert lib.pi_exp(h, 100) == 0
+
+
+def test_a_mesh_is_updated_on_its_own_device(lib):
+    """New positions and the projection grid are made on the mesh's device whichever is
+    current, and the current one stays."""
+    X, F = _canonical("icosphere")
+    h, seen = lib.mesh(X, F), []
+    lib.L.fake_set_device(1)
+    try:
+        with lib.on_launch(lambda name, dev, args: seen.append((name, dev))):
+            assert lib.L.sg_mesh_update_vertices(h, fake_hip.ptr(X), len(X)) == 0
+            assert lib.pi_exp(h, 100) == 0
+        assert lib.L.fake_device() == 1
+    finally:
+        lib.L.fake_set_device(0)
+    where = dict(seen)
+    assert where.pop("k_pi_exp_grid") == 1   # (the call's own kernel: the caller's stream)
+    assert {"k_pos_check", "k_pos_faces", "k_pos_vertices", "k_pi_faces", "k_pi_fill"} <= set(where)
+    assert set(where.values()) == {0}, where

@@ -145,9 +145,11 @@ def _with_workspace(o: Opts, need: int, dev):
     The library's own stream-ordered allocation goes back to the driver at the next synchronisation and is mapped
     again by the next call: 0.4 ms a call at 1M rays, 50 to 370 ms with the vertex gradient's records.  PyTorch's
     allocator keeps the block, hands it out again in stream order, and gives it back with torch.cuda.empty_cache().
-    A caller's workspace is used as it is; if PyTorch has no memory left the library's allocation decides."""
+    A caller's workspace is used as it is; if PyTorch has no memory left the library's allocation decides, and so it does
+    with tensors of another device than the current one: the launches go to the current device's stream, and a block of
+    the other device would be handed out again in the order of that device's."""
     import torch
-    if need == 0 or o.workspace:
+    if need == 0 or o.workspace or dev.index != torch.cuda.current_device():
         return o, None
     try:
         ws = torch.empty(need, dtype=torch.uint8, device=dev)

@@ -105,8 +105,10 @@ typedef struct {
                               the backward (the vertex gradient leaves out rays that slid) */
     int32_t gradx_records; /* vertex gradient: edge crossings per query for which the workspace holds records
                               (48 bytes each, at most 2^30 records per call; up to 4,194,304 half-edges twice
-                              as many of 24 bytes) that are summed per half-edge in LDS; crossings past them
-                              add their sums with float64 atomics (same result, slower).  0: 256; < 0: none */
+                              as many of 24 bytes) that are summed per half-edge in LDS; besides them it holds
+                              partly filled chunks, up to as much again or 192 KB per block of walk_blocks
+                              (151 MB with 768), whichever is more; crossings past them add their sums with
+                              float64 atomics (same result, slower).  0: 256; < 0: none */
     void* workspace;       /* optional caller-owned device workspace, 256-byte aligned, at least the size
                               sg_exp_workspace_size / sg_backward_workspace_size report.  With it a call
                               allocates nothing, so it can be captured in a HIP graph (debug bit 2 aside).

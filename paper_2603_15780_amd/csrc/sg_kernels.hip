@@ -1554,6 +1554,7 @@ SG_HD __forceinline__ void gx_cross(double* acc, const Ray& st, const float4& c,
 // the bin's totals to the half-edge sums once.  Crossings past a block's
 // chunks fall back to the atomics.
 constexpr int kGxChunk = 1024;            // records per chunk
+constexpr int kGxOpenChunks = 4;          // per block: one partly filled chunk for each of its waves
 constexpr int kGxMaxBins = 4096;          // bins (LDS counters of the walk and of the scatter)
 constexpr int kGxWindow = 4096;           // half-edges summed in LDS at once by the reduce pass (160 KB)
 constexpr int kGxShift0 = 12;             // log2 of the smallest bin: one reduce window
@@ -3597,32 +3598,39 @@ static BwdLayout bwd_layout(int64_t n, const BwdPlan& P, bool gradx, int64_t n_f
     if (!L.sorted)
         while (bins_at(L.shift) > kGxMaxBins) ++L.shift;
     L.blocks = std::max(walk_blocks, 1);
+    // sorted records: twice gx_records per query (they have no sorted copy), and room for
+    // a partly filled chunk per (wave, bin): up to as much again, or to what the other
+    // form's blocks hold besides their shares, so that a budget set low for its memory
+    // stays low.  Streams that get no chunk add their sums with atomics
+    const int64_t want = (2 * (int64_t)n * std::max(gx_records, 0) + kGsChunk - 1) / kGsChunk;
+    const int64_t open = std::max(want, (int64_t)L.blocks * kGxOpenChunks * 2 * kGxChunk / kGsChunk);
     if (L.sorted && cus > 0) {
         // every wave keeps a stream per bin and its buffer, so fewer waves are better
         // until each lane has two rays: 100,003 queries on 81,920 faces take 441,
         // 498 and 543 us (backward) with one, two and three blocks per CU, 300,000
         // take 1007, 753 and 814, 1,048,576 on 327,680 faces are fastest with three;
-        // no more blocks than waves of rays
+        // no more blocks than waves of rays.  Down to half as many where that gives
+        // every stream its chunk (20,011 queries on 1,310,720 faces, 156 blocks: 1,478 us,
+        // with 256 blocks 1,516, and 1,608 with room for two thirds of the streams)
         const int64_t per = std::min<int64_t>(std::max<int64_t>((n + 256 * (int64_t)cus) / (512 * (int64_t)cus), 1),
                                               bins_at(L.shift) > 256 ? 2 : 3);
         L.blocks = (int)std::min<int64_t>(per * cus, std::max<int64_t>((n + 63) / 64, 1));
+        if (gx_records > 0)
+            L.blocks = (int)std::max<int64_t>(std::min<int64_t>(L.blocks, open / (4 * std::max(bins_at(L.shift), 1))), (L.blocks + 1) / 2);
     }
     const int64_t nblk = L.blocks;
     size_t chunk_bytes = kGxChunk * sizeof(GxRec);
     if (gradx && gx_records > 0 && nh > 0) {
         L.nbins = bins_at(L.shift);
         if (L.sorted) {
-            // twice gx_records per query (the records have no sorted copy), shared evenly by
-            // the walk blocks (the persistent walk balances crossings across them), plus
-            // one partly filled chunk per (wave, bin)
-            const int64_t want = (2 * (int64_t)n * gx_records + kGsChunk - 1) / kGsChunk;
-            L.per_block = (int)std::min<int64_t>(
-                std::min<int64_t>((want + nblk - 1) / nblk, 2 * kGxMaxRecords / kGsChunk / nblk - 4 * L.nbins) + 4 * L.nbins,
-                kGsMaxBlockChunks);
+            // (shared evenly by the walk blocks: the persistent walk balances crossings across them)
+            const int64_t most = 2 * kGxMaxRecords / kGsChunk / nblk;
+            const int64_t extra = std::min(std::min<int64_t>(4 * L.nbins, open / nblk), most);
+            L.per_block = (int)std::min<int64_t>(std::min((want + nblk - 1) / nblk, most - extra) + extra, kGsMaxBlockChunks);
             chunk_bytes = kGsChunk * sizeof(GxRec);
         } else {
             const int64_t want = ((int64_t)n * gx_records + kGxChunk - 1) / kGxChunk;
-            L.per_block = (int)std::min<int64_t>((want + nblk - 1) / nblk + 4, kGxMaxRecords / kGxChunk / nblk);
+            L.per_block = (int)std::min<int64_t>((want + nblk - 1) / nblk + kGxOpenChunks, kGxMaxRecords / kGxChunk / nblk);
         }
     }
     const int64_t nchunks = L.per_block * nblk;

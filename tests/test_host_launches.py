@@ -134,3 +134,24 @@ def test_a_mesh_is_updated_on_its_own_device(lib):
     assert where.pop("k_pi_exp_grid") == 1   # (the call's own kernel: the caller's stream)
     assert {"k_pos_check", "k_pos_faces", "k_pos_vertices", "k_pi_faces", "k_pi_fill"} <= set(where)
     assert set(where.values()) == {0}, where
+
+
+@pytest.fixture(scope="module")
+def wide(lib):   # 350,284 faces: 257 bins of records, the smallest mesh of the larger kernel
+    return lib.mesh(*M.canonical(*M.torus_grid(419, 418, 0.2, np.random.default_rng(1))))
+
+
+@pytest.mark.parametrize("records", [1, 4, 32, 256])
+@pytest.mark.parametrize("n", [100, 5000, 20011, 300000])
+def test_record_budget_bounds_the_workspace(lib, wide, n, records):
+    """gradx_records says how much memory the vertex gradient's records take: 48 bytes
+    each, and for the partly filled chunks as much again or 192 KB for each of the
+    default 768 blocks, whichever is more; with two words per 384-byte chunk and the
+    block counts."""
+    def need(records):
+        out, o = C.c_size_t(), sg.opts(gradx_records=records)
+        assert lib.L.sg_backward_workspace_size(wide, sg.BWD_EP, n, 0, 1, C.byref(o), C.byref(out)) == 0
+        return out.value
+
+    budget = 48 * n * records
+    assert need(records) - need(-1) <= (1 + 8 / 384) * (budget + max(budget, 768 * 196608)) + (4 << 20)

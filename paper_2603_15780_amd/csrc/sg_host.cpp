@@ -383,7 +383,7 @@ int build_pi(sg_mesh m) {
     if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
     if (e == hipSuccess) e = sg::launch_pi_faces(M, m->d_piface, nullptr);
     // the grids
-    uint64_t total = 0, entries = 0;
+    uint64_t total = 0, entries[2] = {0, 0};   // cells; cell entries, and the faces that have very many
     double pad = 0.0;
     for (const double edges : {0.65, 1.0, 1.5}) {
         const bool last = edges == 1.5;
@@ -398,20 +398,21 @@ int build_pi(sg_mesh m) {
         auto* sum = reinterpret_cast<unsigned long long*>(tmp);
         if (e == hipSuccess) e = hipMemcpy(m->d_pigrid, grid.data(), grid.size() * sizeof(sg::PiGrid), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(), sum, pad, nullptr);
-        if (e == hipSuccess) e = hipMemcpy(&entries, sum, sizeof entries, hipMemcpyDeviceToHost);
-        if (e != hipSuccess || last || entries <= kPiEntries * (uint64_t)m->n_faces) break;
+        if (e == hipSuccess) e = hipMemcpy(entries, sum, sizeof entries, hipMemcpyDeviceToHost);
+        if (e != hipSuccess || last || entries[0] <= kPiEntries * (uint64_t)m->n_faces) break;
     }
     (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "projection grid");
-    if (total >= ((uint64_t)1 << 31) || entries >= ((uint64_t)1 << 32) - 1) return fail(SG_E_OOM, "projection grid too large");
-    const size_t cell_bytes = (total + 2 + (uint64_t)sg::scan_tiles((int64_t)total + 1)) * sizeof(uint32_t);
+    if (total >= ((uint64_t)1 << 31) || entries[0] >= ((uint64_t)1 << 32) - 1) return fail(SG_E_OOM, "projection grid too large");
+    const int64_t n_large = (int64_t)entries[1];
+    const size_t cell_bytes = (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + (uint64_t)n_large) * sizeof(uint32_t);
     e = hipMalloc((void**)&m->d_cell_start, cell_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&m->d_cell_face, std::max<uint64_t>(entries, 1) * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMalloc((void**)&m->d_cell_face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
     if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
-    m->pi_bytes += cell_bytes + (size_t)entries * sizeof(int32_t);
-    uint32_t* cells = m->d_cell_start + 1;
-    e = sg::launch_pi_count(m->pi(), cells, (int64_t)total, pad, cells + total + 1, nullptr);
-    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(), cells, m->d_cell_face, pad, nullptr);
+    m->pi_bytes += cell_bytes + (size_t)entries[0] * sizeof(int32_t);
+    uint32_t *cells = m->d_cell_start + 1, *large = cells + total + 1, *tile = large + 1 + n_large;
+    e = sg::launch_pi_count(m->pi(), cells, (int64_t)total, pad, tile, large, n_large, nullptr);
+    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(), cells, m->d_cell_face, pad, large, n_large, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // later calls read it on any stream
     if (e != hipSuccess) return hip_fail(e, "projection grid");
     return SG_OK;

@@ -664,42 +664,79 @@ __device__ __forceinline__ void face_box(const PiMesh& P, const PiGrid& G, int64
     }
 }
 
+__device__ __forceinline__ unsigned long long box_cells(const int (&i0)[3], const int (&i1)[3]) {
+    return (unsigned long long)(i1[0] - i0[0] + 1) * (unsigned long long)(i1[1] - i0[1] + 1) *
+           (unsigned long long)(i1[2] - i0[2] + 1);
+}
+
+// A face's cells, one lane per face; faces of more than kPiLane cells are left to
+// k_pi_large.  (With a tetrahedron over a mesh of 20,480 faces the grid took 69 ms,
+// its four faces in four lanes with a cell in each every 0.1 us; now 1.1.)
+constexpr unsigned long long kPiLane = 512;
+
 template <class Add>
-__device__ __forceinline__ void face_cells(const PiMesh& P, int64_t u, double pad, Add&& add) {
+__device__ __forceinline__ bool face_cells(const PiMesh& P, int64_t u, double pad, Add&& add) {
     const PiGrid G = P.grid[mesh_of(P, (int32_t)u)];
     int i0[3], i1[3];
     face_box(P, G, u, pad, i0, i1);
+    if (box_cells(i0, i1) > kPiLane) return false;
     for (int iz = i0[2]; iz <= i1[2]; ++iz)
         for (int iy = i0[1]; iy <= i1[1]; ++iy)
             for (int ix = i0[0]; ix <= i1[0]; ++ix) add(G.cell0 + (uint32_t)((iz * G.ny + iy) * G.nx + ix));
+    return true;
 }
 
 __global__ __launch_bounds__(256) void k_pi_zero(uint32_t* x, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) x[i] = 0u;
 }
 
-// All faces' cells, added up in 64 bits without visiting them (a few large faces can meet very many).
+// All faces' cells (sum[0]), added up in 64 bits without visiting them (a few large faces can meet very many), and
+// the faces of more than kPiLane (sum[1]).
 __global__ __launch_bounds__(256) void k_pi_entries(PiMesh P, unsigned long long* sum, double pad) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     unsigned long long n = 0ull;
     if (u < P.n_faces) {
         int i0[3], i1[3];
         face_box(P, P.grid[mesh_of(P, (int32_t)u)], u, pad, i0, i1);
-        n = 1ull;
-        for (int c = 0; c < 3; ++c) n *= (unsigned long long)(i1[c] - i0[c] + 1);
+        n = box_cells(i0, i1);
     }
+    if (n > kPiLane) atomicAdd(sum + 1, 1ull);
     for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
     if ((threadIdx.x & 63u) == 0u) atomicAdd(sum, n);
 }
 
-__global__ __launch_bounds__(256) void k_pi_count(PiMesh P, uint32_t* cells, double pad) {
+// large: the number of faces left to k_pi_large, then these
+__global__ __launch_bounds__(256) void k_pi_count(PiMesh P, uint32_t* cells, double pad, uint32_t* large) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < P.n_faces) face_cells(P, u, pad, [&](uint32_t c) { atomicAdd(cells + c, 1u); });
+    if (u < P.n_faces && !face_cells(P, u, pad, [&](uint32_t c) { atomicAdd(cells + c, 1u); }))
+        large[1u + atomicAdd(large, 1u)] = (uint32_t)u;
 }
 
 __global__ __launch_bounds__(256) void k_pi_fill(PiMesh P, uint32_t* cells, int32_t* cell_face, double pad) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < P.n_faces) face_cells(P, u, pad, [&](uint32_t c) { cell_face[atomicAdd(cells + c, 1u)] = (int32_t)u; });
+    if (u < P.n_faces)
+        (void)face_cells(P, u, pad, [&](uint32_t c) { cell_face[atomicAdd(cells + c, 1u)] = (int32_t)u; });
+}
+
+// The large faces, a row of blocks each.
+template <bool kFill>
+__global__ __launch_bounds__(256) void k_pi_large(PiMesh P, const uint32_t* large, uint32_t* cells, int32_t* cell_face,
+                                                  double pad) {
+    const uint32_t n_large = large[0];
+    for (uint32_t k = blockIdx.y; k < n_large; k += gridDim.y) {
+        const int32_t u = (int32_t)large[1u + k];
+        const PiGrid G = P.grid[mesh_of(P, u)];
+        int i0[3], i1[3];
+        face_box(P, G, u, pad, i0, i1);
+        const uint32_t nx = (uint32_t)(i1[0] - i0[0] + 1), ny = (uint32_t)(i1[1] - i0[1] + 1), n = nx * ny * (uint32_t)(i1[2] - i0[2] + 1);
+        for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
+            const uint32_t row = i / nx, iz = row / ny;
+            const int ix = i0[0] + (int)(i - row * nx), iy = i0[1] + (int)(row - iz * ny);
+            const uint32_t c = G.cell0 + (uint32_t)(((i0[2] + (int)iz) * G.ny + iy) * G.nx + ix);
+            if (kFill) cell_face[atomicAdd(cells + c, 1u)] = u;
+            else atomicAdd(cells + c, 1u);
+        }
+    }
 }
 
 // The grid search's ray order: rays by start face, kPiBuckets stretches of the
@@ -962,21 +999,34 @@ hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, hipStream_t s) {
 }
 
 hipError_t launch_pi_entries(const PiMesh& P, unsigned long long* sum, double pad, hipStream_t s) {
-    hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(sum), (int64_t)2);
+    hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(sum), (int64_t)4);
     hipLaunchKernelGGL(k_pi_entries, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, sum, pad);
     return hipGetLastError();
 }
 
-hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, double pad, uint32_t* tile, hipStream_t s) {
+static void large_faces(const PiMesh& P, int64_t n_large, const uint32_t* large, uint32_t* cells, int32_t* cell_face, double pad,
+                        hipStream_t s) {
+    const dim3 grid(64, (unsigned)std::min<int64_t>(n_large, 1024)), block(256);
+    if (n_large == 0) return;
+    if (cell_face) hipLaunchKernelGGL((k_pi_large<true>), grid, block, 0, s, P, large, cells, cell_face, pad);
+    else hipLaunchKernelGGL((k_pi_large<false>), grid, block, 0, s, P, large, cells, cell_face, pad);
+}
+
+hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, double pad, uint32_t* tile, uint32_t* large,
+                           int64_t n_large, hipStream_t s) {
     hipLaunchKernelGGL(k_pi_zero, dim3((unsigned)std::min<int64_t>((total + 256) / 256, 8192)), dim3(256), 0, s, cells - 1,
                        total + 2);
-    hipLaunchKernelGGL(k_pi_count, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, cells, pad);
+    hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, large, (int64_t)1);
+    hipLaunchKernelGGL(k_pi_count, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, cells, pad, large);
+    large_faces(P, n_large, large, cells, nullptr, pad, s);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? launch_scan(cells, total + 1, tile, s) : e;
 }
 
-hipError_t launch_pi_fill(const PiMesh& P, uint32_t* cells, int32_t* cell_face, double pad, hipStream_t s) {
+hipError_t launch_pi_fill(const PiMesh& P, uint32_t* cells, int32_t* cell_face, double pad, const uint32_t* large,
+                          int64_t n_large, hipStream_t s) {
     hipLaunchKernelGGL(k_pi_fill, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, cells, cell_face, pad);
+    large_faces(P, n_large, large, cells, cell_face, pad, s);
     return hipGetLastError();
 }
 

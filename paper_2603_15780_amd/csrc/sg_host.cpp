@@ -53,17 +53,23 @@ struct sg_mesh_s {
     sg::PackedMesh host;   // face order, mesh offsets and edge count
     void* d_pos = nullptr;   // sg_mesh_update_vertices: the new positions before they are accepted (kept)
     // projection-integration Exp: per-face data in user order and one grid per
-    // mesh, built on the first call that needs them (and again after a vertex update)
+    // mesh, in fine cells for short steps and coarse ones for long steps, each built
+    // on the first call that needs it (and again after a vertex update)
+    struct PiCells {
+        sg::PiGrid* grid = nullptr;
+        uint32_t* start = nullptr;
+        int32_t* face = nullptr;
+        bool ready = false;
+    };
     std::mutex pi_mu;
-    bool pi_ready = false;
     sg::PiFace* d_piface = nullptr;
-    sg::PiGrid* d_pigrid = nullptr;
-    uint32_t* d_cell_start = nullptr;
-    int32_t* d_cell_face = nullptr;
-    size_t pi_bytes = 0;
+    PiCells pi_cells[2];
+    std::vector<double> pi_ext;   // the meshes' extents
+    double pi_edge = 0.0;         // the smallest mean edge of a mesh
     double pi_tie = 0.0, pi_slack = 0.0;
-    sg::PiMesh pi() const {
-        return sg::PiMesh{d_piface, d_pigrid, d_cell_start, d_cell_face, n_faces, n_meshes, pi_tie, pi_slack};
+    sg::PiMesh pi(int cells) const {
+        const PiCells& c = pi_cells[cells];
+        return sg::PiMesh{d_piface, c.grid, c.start, c.face, n_faces, n_meshes, pi_tie, pi_slack};
     }
     sg::DevMesh dev(int32_t hole_avoid = 0) const {
         sg::DevMesh d{d_face,  d_F,     d_X,     d_half, d_perm,     d_order,
@@ -158,17 +164,18 @@ int upload(T** dptr, const std::vector<T>& h, size_t& bytes) {
     return SG_OK;
 }
 
+void free_pi_cells(sg_mesh_s::PiCells& c) {
+    (void)hipFree(c.grid);
+    (void)hipFree(c.start);
+    (void)hipFree(c.face);
+    c = sg_mesh_s::PiCells{};
+}
+
 void free_pi(sg_mesh_s* m) {
+    for (auto& c : m->pi_cells) free_pi_cells(c);
     (void)hipFree(m->d_piface);
-    (void)hipFree(m->d_pigrid);
-    (void)hipFree(m->d_cell_start);
-    (void)hipFree(m->d_cell_face);
     m->d_piface = nullptr;
-    m->d_pigrid = nullptr;
-    m->d_cell_start = nullptr;
-    m->d_cell_face = nullptr;
-    m->pi_bytes = 0;
-    m->pi_ready = false;
+    m->pi_ext.clear();
 }
 
 void free_mesh(sg_mesh_s* m) {
@@ -348,90 +355,115 @@ uint64_t pi_grids(const std::vector<int64_t>& fo, const std::vector<double>& ext
     return total;
 }
 
-// Builds the projection-integration data of a handle on the device: per-face
-// records in user order and one uniform grid per mesh whose cells list the faces
-// whose bounding boxes, widened by a margin, meet them.  Cells are 0.65 mean
-// edges wide: a smooth mesh's query then tests 6 faces instead of 11 with one
-// edge and 18 with 1.5 (131,072 rays on 327,680 faces: 1.52, 2.11 and 3.65 ms;
-// finer ones cost more than they save where steps leave the surface: on a rough
-// mesh 8.7 ms with one edge, 9.7 with 0.65, 11.0 with 0.5).  A mesh whose faces
-// differ so much in size that they meet kPiEntries cells each gets wider ones,
-// up to 1.5 edges.
+// The projection-integration data of a handle, built on the device: per-face
+// records in user order and, per mesh, uniform grids whose cells list the faces
+// whose bounding boxes, widened by a margin, meet them.
+// Steps of up to kPiLongStep mean edges take cells of 0.65 mean edges: a smooth
+// mesh's query then tests 6 faces instead of 11 with one edge and 18 with 1.5
+// (131,072 rays on 327,680 faces: 1.52, 2.11 and 3.65 ms).  A mesh whose faces
+// differ so much in size that they meet kPiEntries cells each gets wider ones, up
+// to 1.5 edges.  Longer steps leave the surface by many cells, and a query looks
+// through some (2 d / cell)^3 of them d away from it: they take cells of 1.5 edges.
+// 2,048 rays, ms with cells of 0.65 and 1.5 edges: on 20,480 faces, steps of 1.7
+// edges 2.8 and 3.6, of 2.9 5.2 and 4.1, of 5.8 34 and 14, of 29 1,892 and 260; on
+// 81,920 faces 3.5 edges 2.7 and 3.0, 5.8 4.2 and 4.2, 12 37 and 13; on 327,680
+// faces 12 edges 1.9 and 2.8, 23 9.1 and 4.1; on a rough mesh of 81,920 faces 1.7
+// edges 15 and 20, 3.5 21 and 19, 5.8 31 and 21.
 // Called with pi_mu held; on failure the caller frees what was allocated.
 constexpr uint64_t kPiEntries = 64;   // (a smooth mesh: 12)
+constexpr double kPiLongStep = 6.0;
 
-int build_pi(sg_mesh m) {
-    const sg::PackedMesh& pm = m->host;
-    const std::vector<int64_t>& fo = pm.face_off;
+int build_pi_faces(sg_mesh m) {
+    const std::vector<int64_t>& fo = m->host.face_off;
     const int nm = (int)fo.size() - 1;
     const sg::DevMesh M = m->dev();
-    // extents of each mesh, and the face records
     std::vector<double> ext((size_t)nm * sg::kPiParts * sg::kPiExtent);
-    std::vector<sg::PiGrid> grid(nm);
-    int rc = upload(&m->d_pigrid, grid, m->pi_bytes);
-    if (rc != SG_OK) return rc;
-    const size_t face_bytes = (size_t)m->n_faces * sizeof(sg::PiFace);
     const size_t off_bytes = (fo.size() * sizeof(int64_t) + 255) & ~(size_t)255;
     void* tmp = nullptr;
-    hipError_t e = hipMalloc((void**)&m->d_piface, face_bytes);
+    hipError_t e = hipMalloc((void**)&m->d_piface, (size_t)m->n_faces * sizeof(sg::PiFace));
     if (e == hipSuccess) e = hipMalloc(&tmp, off_bytes + ext.size() * sizeof(double));
     if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
-    m->pi_bytes += face_bytes;
     double* d_ext = reinterpret_cast<double*>(reinterpret_cast<char*>(tmp) + off_bytes);
     e = hipMemcpy(tmp, fo.data(), fo.size() * sizeof(int64_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = sg::launch_pi_extents(M, reinterpret_cast<const int64_t*>(tmp), nm, d_ext, nullptr);
     if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
     if (e == hipSuccess) e = sg::launch_pi_faces(M, m->d_piface, nullptr);
-    // the grids
+    (void)hipFree(tmp);
+    if (e != hipSuccess) return hip_fail(e, "projection grid");
+    m->pi_edge = INFINITY;
+    for (int k = 0; k < nm; ++k) {
+        double el = 0.0;
+        for (int p = 0; p < sg::kPiParts; ++p) el += ext[((size_t)k * sg::kPiParts + p) * sg::kPiExtent + 6];
+        if (fo[k + 1] > fo[k]) m->pi_edge = std::min(m->pi_edge, el / (3.0 * (double)(fo[k + 1] - fo[k])));
+    }
+    m->pi_ext = std::move(ext);
+    return SG_OK;
+}
+
+int build_pi_cells(sg_mesh m, int set) {
+    const std::vector<int64_t>& fo = m->host.face_off;
+    std::vector<sg::PiGrid> grid(fo.size() - 1);
+    sg_mesh_s::PiCells& c = m->pi_cells[set];
+    const size_t grid_bytes = grid.size() * sizeof(sg::PiGrid), sum_at = (grid_bytes + 255) & ~(size_t)255;
+    hipError_t e = hipMalloc((void**)&c.grid, sum_at + 16);
+    if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
+    auto* sum = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(c.grid) + sum_at);
     uint64_t total = 0, entries[2] = {0, 0};   // cells; cell entries, and the faces that have very many
     double pad = 0.0;
     for (const double edges : {0.65, 1.0, 1.5}) {
         const bool last = edges == 1.5;
+        if (set == 1 && !last) continue;
         double scale;
-        total = pi_grids(fo, ext, edges, edges < 1.0 ? 128 : 32, grid, scale);
+        total = pi_grids(fo, m->pi_ext, edges, edges < 1.0 ? 128 : 32, grid, scale);
         if (total >= ((uint64_t)1 << 31)) continue;
         // distances within 1e-12 of the largest coordinate are one nearest point (float64 rounding);
         // the cell search reaches 1e-9 further, past any rounding of a box distance
         m->pi_tie = 1e-12 * scale;
         m->pi_slack = 1e-9 * scale;
         pad = scale * std::ldexp(1.0, -20);
-        auto* sum = reinterpret_cast<unsigned long long*>(tmp);
-        if (e == hipSuccess) e = hipMemcpy(m->d_pigrid, grid.data(), grid.size() * sizeof(sg::PiGrid), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(), sum, pad, nullptr);
+        e = hipMemcpy(c.grid, grid.data(), grid_bytes, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(set), sum, pad, nullptr);
         if (e == hipSuccess) e = hipMemcpy(entries, sum, sizeof entries, hipMemcpyDeviceToHost);
         if (e != hipSuccess || last || entries[0] <= kPiEntries * (uint64_t)m->n_faces) break;
     }
-    (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "projection grid");
     if (total >= ((uint64_t)1 << 31) || entries[0] >= ((uint64_t)1 << 32) - 1) return fail(SG_E_OOM, "projection grid too large");
     const int64_t n_large = (int64_t)entries[1];
-    const size_t cell_bytes = (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + (uint64_t)n_large) * sizeof(uint32_t);
-    e = hipMalloc((void**)&m->d_cell_start, cell_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&m->d_cell_face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
+    e = hipMalloc((void**)&c.start,
+                  (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + (uint64_t)n_large) * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc((void**)&c.face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
     if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
-    m->pi_bytes += cell_bytes + (size_t)entries[0] * sizeof(int32_t);
-    uint32_t *cells = m->d_cell_start + 1, *large = cells + total + 1, *tile = large + 1 + n_large;
-    e = sg::launch_pi_count(m->pi(), cells, (int64_t)total, pad, tile, large, n_large, nullptr);
-    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(), cells, m->d_cell_face, pad, large, n_large, nullptr);
+    uint32_t *cells = c.start + 1, *large = cells + total + 1, *tile = large + 1 + n_large;
+    e = sg::launch_pi_count(m->pi(set), cells, (int64_t)total, pad, tile, large, n_large, nullptr);
+    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(set), cells, c.face, pad, large, n_large, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // later calls read it on any stream
     if (e != hipSuccess) return hip_fail(e, "projection grid");
     return SG_OK;
 }
 
-int ensure_pi(sg_mesh m) {
+// out: the handle's data with the cells for steps of this length
+int ensure_pi(sg_mesh m, double step, sg::PiMesh& out) {
     std::lock_guard<std::mutex> lock(m->pi_mu);
-    if (m->pi_ready) return SG_OK;
-    const OnDevice dev(m->device);
-    if (dev.err != hipSuccess) return hip_fail(dev.err, "projection grid");
-    int rc;
-    try {
-        rc = build_pi(m);
-    } catch (const std::bad_alloc&) {
-        rc = fail(SG_E_OOM, "out of host memory");
+    auto cells = [&] { return step > kPiLongStep * m->pi_edge ? 1 : 0; };
+    if (m->pi_ext.empty() || !m->pi_cells[cells()].ready) {
+        const OnDevice dev(m->device);
+        if (dev.err != hipSuccess) return hip_fail(dev.err, "projection grid");
+        int rc = SG_OK;
+        try {
+            if (m->pi_ext.empty()) rc = build_pi_faces(m);
+            if (rc == SG_OK) rc = build_pi_cells(m, cells());
+        } catch (const std::bad_alloc&) {
+            rc = fail(SG_E_OOM, "out of host memory");
+        }
+        if (rc != SG_OK) {
+            if (!m->pi_cells[0].ready && !m->pi_cells[1].ready) free_pi(m);
+            else free_pi_cells(m->pi_cells[cells()]);
+            return rc;
+        }
+        m->pi_cells[cells()].ready = true;
     }
-    if (rc == SG_OK) m->pi_ready = true;
-    else free_pi(m);
-    return rc;
+    out = m->pi(cells());
+    return SG_OK;
 }
 
 int check_pi_opts(const sg_pi_opts* in, sg_pi_opts& o) {
@@ -1232,7 +1264,8 @@ int sg_pi_exp(sg_mesh mesh, int64_t n, const int32_t* f, const float* b, const f
     if (n == 0) return SG_OK;
     if (!f || !b || !v || !f_out || !b_out || !p_out || !v_out) return fail(SG_E_ARG, "a required array is NULL");
     if (K > 0 && (!W || !W_out)) return fail(SG_E_ARG, "W and W_out are required when K > 0");
-    rc = ensure_pi(mesh);
+    sg::PiMesh P;
+    rc = ensure_pi(mesh, po.step, P);
     if (rc != SG_OK) return rc;
     sg::PiArgs a{};
     a.n = n;
@@ -1256,7 +1289,7 @@ int sg_pi_exp(sg_mesh mesh, int64_t n, const int32_t* f, const float* b, const f
             (void)hipGetLastError();
         }
     }
-    hipError_t e = sg::launch_pi_exp(mesh->pi(), mesh->dev(), a, ws.p, st);
+    hipError_t e = sg::launch_pi_exp(P, mesh->dev(), a, ws.p, st);
     const hipError_t e2 = give_workspace(ws, st);
     if (e != hipSuccess) return hip_fail(e, "PI launch");
     if (e2 != hipSuccess) return hip_fail(e2, "workspace release");
@@ -1287,7 +1320,8 @@ int sg_pi_backward(sg_mesh mesh, int32_t mode, int64_t n, const int32_t* f, cons
     if (!f || !b || !v || !g_p || !grad_v || !grad_b) return fail(SG_E_ARG, "a required array is NULL");
     if (mode == SG_BWD_EP && (!f_out || !v_out)) return fail(SG_E_ARG, "EP needs the forward's f_out and v_out");
     if (n >= ((int64_t)1 << 29)) return fail(SG_E_ARG, "the PI backward takes fewer than 2^29 queries per call");
-    rc = ensure_pi(mesh);
+    sg::PiMesh P;
+    rc = ensure_pi(mesh, po.step, P);
     if (rc != SG_OK) return rc;
     sg::BwdArgs a{};
     a.n = n;
@@ -1307,7 +1341,7 @@ int sg_pi_backward(sg_mesh mesh, int32_t mode, int64_t n, const int32_t* f, cons
     Workspace ws;
     rc = take_workspace(o, sg::pi_bwd_workspace(n, mode), st, ws);
     if (rc != SG_OK) return rc;
-    hipError_t e = sg::launch_pi_backward(mesh->pi(), mesh->dev(), a, pa, ws.p, st);
+    hipError_t e = sg::launch_pi_backward(P, mesh->dev(), a, pa, ws.p, st);
     const hipError_t e2 = give_workspace(ws, st);
     if (e != hipSuccess) return hip_fail(e, "PI backward launch");
     if (e2 != hipSuccess) return hip_fail(e2, "workspace release");

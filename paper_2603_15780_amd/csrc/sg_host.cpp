@@ -424,15 +424,20 @@ int build_pi_cells(sg_mesh m, int set) {
         e = hipMemcpy(c.grid, grid.data(), grid_bytes, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(set), sum, pad, nullptr);
         if (e == hipSuccess) e = hipMemcpy(entries, sum, sizeof entries, hipMemcpyDeviceToHost);
-        if (e != hipSuccess || last || entries[0] <= kPiEntries * (uint64_t)m->n_faces) break;
+        if (e != hipSuccess) return hip_fail(e, "projection grid");
+        if (!last && entries[0] > kPiEntries * (uint64_t)m->n_faces) continue;
+        if (entries[0] >= ((uint64_t)1 << 32) - 1) break;
+        e = hipMalloc((void**)&c.start,
+                      (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + entries[1]) * sizeof(uint32_t));
+        if (e == hipSuccess) e = hipMalloc((void**)&c.face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
+        if (e == hipSuccess) break;
+        (void)hipGetLastError();   // no memory for these: wider cells take less
+        (void)hipFree(c.start);
+        c.start = nullptr;
+        if (last) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
     }
-    if (e != hipSuccess) return hip_fail(e, "projection grid");
-    if (total >= ((uint64_t)1 << 31) || entries[0] >= ((uint64_t)1 << 32) - 1) return fail(SG_E_OOM, "projection grid too large");
+    if (!c.start) return fail(SG_E_OOM, "projection grid too large");
     const int64_t n_large = (int64_t)entries[1];
-    e = hipMalloc((void**)&c.start,
-                  (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + (uint64_t)n_large) * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&c.face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
-    if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
     uint32_t *cells = c.start + 1, *large = cells + total + 1, *tile = large + 1 + n_large;
     e = sg::launch_pi_count(m->pi(set), cells, (int64_t)total, pad, tile, large, n_large, nullptr);
     if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(set), cells, c.face, pad, large, n_large, nullptr);

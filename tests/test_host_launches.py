@@ -155,3 +155,25 @@ def test_record_budget_bounds_the_workspace(lib, wide, n, records):
 
     budget = 48 * n * records
     assert need(records) - need(-1) <= (1 + 8 / 384) * (budget + max(budget, 768 * 196608)) + (4 << 20)
+
+
+@pytest.mark.parametrize("limit,rc", [(1 << 20, 0), (400 << 10, 0), (100 << 10, sg.SG_E_OOM)])
+def test_projection_grid_without_memory_for_fine_cells(lib, limit, rc):
+    """1,280 faces of edge 0.02 in a box of 1: 128 cells a face (up to 655 KB) in fine
+    cells, 32 (164 KB) in wide ones, which a handle whose fine cells do not fit takes."""
+    h = lib.mesh(*_canonical("icosphere"))
+
+    def extents(name, dev, args):
+        if name == "k_pi_extents":
+            out = C.cast(args[2], C.POINTER(C.POINTER(C.c_double))).contents
+            for part in range(16):
+                for k, x in enumerate((0.0, 0.0, 0.0, 1.0, 1.0, 1.0, 3 * 1280 * 0.02 / 16, 1.0)):
+                    out[8 * part + k] = x
+
+    with lib.on_launch(extents):
+        lib.L.fake_malloc_limit(limit)
+        try:
+            assert lib.pi_exp(h, 100) == rc
+        finally:
+            lib.L.fake_malloc_limit(2 ** 63)
+        assert lib.pi_exp(h, 100) == 0

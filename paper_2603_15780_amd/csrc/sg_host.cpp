@@ -97,6 +97,12 @@ int hip_fail(hipError_t e, const char* what) {
     return fail(SG_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+// A failed allocation: reported here, and not again by the next launch's check.
+int no_memory(hipError_t e, const char* what, size_t bytes) {
+    (void)hipGetLastError();
+    return fail(SG_E_OOM, "%s (%zu bytes): %s", what, bytes, hipGetErrorString(e));
+}
+
 struct V3 {
     double x, y, z;
 };
@@ -155,7 +161,7 @@ template <class T>
 int upload(T** dptr, const std::vector<T>& h, size_t& bytes) {
     const size_t nb = h.size() * sizeof(T);
     hipError_t e = hipMalloc((void**)dptr, nb ? nb : sizeof(T));
-    if (e != hipSuccess) return fail(SG_E_OOM, "hipMalloc(%zu): %s", nb, hipGetErrorString(e));
+    if (e != hipSuccess) return no_memory(e, "hipMalloc", nb);
     bytes += nb;
     if (nb) {
         e = hipMemcpy(*dptr, h.data(), nb, hipMemcpyHostToDevice);
@@ -263,7 +269,7 @@ int take_workspace(const sg_opts& o, size_t need, hipStream_t st, Workspace& w) 
         return SG_OK;
     }
     hipError_t e = hipMallocAsync(&w.p, need, st);
-    if (e != hipSuccess) return fail(SG_E_OOM, "workspace allocation: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return no_memory(e, "workspace allocation", need);
     w.own = true;
     return SG_OK;
 }
@@ -380,9 +386,10 @@ int build_pi_faces(sg_mesh m) {
     std::vector<double> ext((size_t)nm * sg::kPiParts * sg::kPiExtent);
     const size_t off_bytes = (fo.size() * sizeof(int64_t) + 255) & ~(size_t)255;
     void* tmp = nullptr;
-    hipError_t e = hipMalloc((void**)&m->d_piface, (size_t)m->n_faces * sizeof(sg::PiFace));
+    const size_t face_bytes = (size_t)m->n_faces * sizeof(sg::PiFace);
+    hipError_t e = hipMalloc((void**)&m->d_piface, face_bytes);
     if (e == hipSuccess) e = hipMalloc(&tmp, off_bytes + ext.size() * sizeof(double));
-    if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return no_memory(e, "projection faces", face_bytes);
     double* d_ext = reinterpret_cast<double*>(reinterpret_cast<char*>(tmp) + off_bytes);
     e = hipMemcpy(tmp, fo.data(), fo.size() * sizeof(int64_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = sg::launch_pi_extents(M, reinterpret_cast<const int64_t*>(tmp), nm, d_ext, nullptr);
@@ -406,7 +413,7 @@ int build_pi_cells(sg_mesh m, int set) {
     sg_mesh_s::PiCells& c = m->pi_cells[set];
     const size_t grid_bytes = grid.size() * sizeof(sg::PiGrid), sum_at = (grid_bytes + 255) & ~(size_t)255;
     hipError_t e = hipMalloc((void**)&c.grid, sum_at + 16);
-    if (e != hipSuccess) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return no_memory(e, "projection grid", sum_at + 16);
     auto* sum = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(c.grid) + sum_at);
     uint64_t total = 0, entries[2] = {0, 0};   // cells; cell entries, and the faces that have very many
     double pad = 0.0;
@@ -427,14 +434,14 @@ int build_pi_cells(sg_mesh m, int set) {
         if (e != hipSuccess) return hip_fail(e, "projection grid");
         if (!last && entries[0] > kPiEntries * (uint64_t)m->n_faces) continue;
         if (entries[0] >= ((uint64_t)1 << 32) - 1) break;
-        e = hipMalloc((void**)&c.start,
-                      (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + entries[1]) * sizeof(uint32_t));
+        const size_t bytes = (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + entries[1]) * sizeof(uint32_t);
+        e = hipMalloc((void**)&c.start, bytes);
         if (e == hipSuccess) e = hipMalloc((void**)&c.face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
         if (e == hipSuccess) break;
-        (void)hipGetLastError();   // no memory for these: wider cells take less
+        const int rc = no_memory(e, "projection grid", bytes + entries[0] * sizeof(int32_t));
         (void)hipFree(c.start);
         c.start = nullptr;
-        if (last) return fail(SG_E_OOM, "projection grid: %s", hipGetErrorString(e));
+        if (last) return rc;   // (else wider cells, which take less)
     }
     if (!c.start) return fail(SG_E_OOM, "projection grid too large");
     const int64_t n_large = (int64_t)entries[1];
@@ -886,7 +893,7 @@ int sg_mesh_update_vertices(sg_mesh mesh, const float* X_host, int64_t n_verts) 
         e = hipMalloc(&mesh->d_pos, need);
         if (e != hipSuccess) {
             mesh->d_pos = nullptr;
-            return fail(SG_E_OOM, "hipMalloc(%zu): %s", need, hipGetErrorString(e));
+            return no_memory(e, "vertex update", need);
         }
         mesh->bytes += need;
     }
@@ -1178,7 +1185,8 @@ int sg_autotune(sg_mesh mesh, int64_t n, const int32_t* f, const float* b, const
     const size_t per = 4 + 3 * 12 + (size_t)K * 12 + 4;
     const size_t ws_bytes = sg::exp_persistent_workspace(n, K);
     const size_t out_bytes = (per * (size_t)n + 1024 + 255) & ~(size_t)255;
-    if (hipMalloc(&buf, out_bytes + ws_bytes) != hipSuccess) return fail(SG_E_OOM, "autotune scratch allocation");
+    const hipError_t got = hipMalloc(&buf, out_bytes + ws_bytes);
+    if (got != hipSuccess) return no_memory(got, "autotune scratch allocation", out_bytes + ws_bytes);
     char* q = static_cast<char*>(buf);
     auto carve = [&](size_t bytes) { char* r = q; q += (bytes + 255) & ~(size_t)255; return r; };
     auto* fo = reinterpret_cast<int32_t*>(carve(4 * (size_t)n));

@@ -177,3 +177,23 @@ def test_projection_grid_without_memory_for_fine_cells(lib, limit, rc):
         finally:
             lib.L.fake_malloc_limit(2 ** 63)
         assert lib.pi_exp(h, 100) == 0
+
+
+@pytest.mark.parametrize("call", ["exp", "gfd", "gradx", "pi_exp", "pi_backward", "update", "create"])
+def test_a_failed_allocation_is_reported_once(lib, call):
+    """The next call, with memory, does not find the error of the one before."""
+    X, F = _canonical("icosphere")
+    h, gx = lib.mesh(X, F), fake_hip.arr(len(X), 3, dtype=np.float64)
+    run = {"exp": lambda: lib.exp(h, 100, kernel=sg.KERNEL_PERSISTENT), "gfd": lambda: lib.backward(h, sg.BWD_GFD, 100),
+           "gradx": lambda: lib.backward(h, sg.BWD_EP, 100, grad_X=gx), "pi_exp": lambda: lib.pi_exp(h, 100),
+           "pi_backward": lambda: lib.pi_backward(h, 100),
+           "update": lambda: lib.L.sg_mesh_update_vertices(h, fake_hip.ptr(X), len(X)),
+           "create": lambda: lib.L.sg_mesh_create(fake_hip.ptr(X), len(X), fake_hip.ptr(F), len(F), None, None, 1,
+                                                  C.byref(C.c_void_p()))}[call]
+    lib.L.fake_malloc_limit(0)
+    try:
+        assert run() == sg.SG_E_OOM
+    finally:
+        lib.L.fake_malloc_limit(2 ** 63)
+    assert lib.exp(h, 100, kernel=sg.KERNEL_PLAIN) == 0
+    assert run() == 0

@@ -48,6 +48,7 @@ struct sg_mesh_s {
     int32_t* d_vc = nullptr;
     int32_t part_face[sg::kParts + 1] = {};
     int32_t has_flip = 0;
+    bool open_mesh = false;
     size_t bytes = 0;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timed, spare;   // walk-kernel event pairs
     sg::PackedMesh host;   // face order, mesh offsets and edge count
@@ -247,7 +248,7 @@ int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1
 }
 
 sg::WalkSched sched(const sg_opts& o, const sg_mesh_s* m) {
-    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1, false, false, m->cu_count,
+    return sg::WalkSched{o.walk_blocks, o.refill_min, o.ray_queues, m->n_meshes == 1, m->open_mesh, false, false, m->cu_count,
                          m->bwd_blocks_per_cu};
 }
 
@@ -707,6 +708,7 @@ int pack_mesh(const float* X_host, int64_t n_verts, const int32_t* F_host, int64
         for (const FaceRec& q : out.face)
             for (int k = 0; k < 3; ++k)
                 if (q.nb[k] >= 0 && nb_flip(q.nb[k])) out.has_flip = 1;
+        out.n_boundary = std::count_if(twin.begin(), twin.end(), [](int64_t g) { return g < 0; });
         out.vbnd = std::move(vbnd);
         out.twin.assign(twin.begin(), twin.end());
         out.F = std::move(F);
@@ -849,6 +851,7 @@ int sg_mesh_create(const float* X_host, int64_t n_verts, const int32_t* F_host, 
     m->n_meshes = n_meshes;
     m->mean_edge = pm.mean_edge;
     m->has_flip = pm.has_flip;
+    m->open_mesh = sg::mesh_open(pm.n_boundary, n_faces);
     for (int p = 0; p <= sg::kParts; ++p) m->part_face[p] = (int32_t)pm.part_start[p];
     std::vector<int32_t> order32(pm.order.begin(), pm.order.end());
     // corners of each vertex (3 f + k over internal faces), grouped by vertex

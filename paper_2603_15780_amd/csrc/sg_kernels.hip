@@ -1266,9 +1266,12 @@ constexpr size_t kQueueBytes = (size_t)kMaxQueues * kQueueStride * sizeof(unsign
 // sweep one sector of the mesh instead of the whole disc around the range, so
 // more of what they touch stays in its 4 MB L2: 4,194,304 rays of length up to
 // pi on 1,310,720 faces 19.9 -> 17.1 ms, 1,048,576 on 327,680 faces 1.09 ->
-// 1.06 ms.  A handle of several meshes takes one direction class: its ranges
-// hold whole meshes, which fit the L2 by themselves (16 meshes, 1,400,003 rays:
-// 0.601 ms with one class, 0.633 with six); so does a batch of fewer than four
+// 1.06 ms.  A handle of several meshes takes one direction class: the ranges of
+// many hold whole meshes, which fit the L2 by themselves (16 meshes, 1,400,003 rays:
+// 0.601 ms with one class, 0.633 with six); so does a mesh with many boundaries
+// (mesh_open; 1,400,000 rays, boundary edges per hundred faces and us with six
+// classes and one: 0.4 1,080 and 1,129, 1.1 980 and 996 on 327,680 faces and 597
+// and 590 on 81,920, 1.7 954 and 861, 3.6 547 and 507, 3.7 569 and 543); so does a batch of fewer than four
 // rays per lane, most of which is in flight at once whatever the order (200,003
 // rays on a mesh with holes: 0.942 ms with one class, 1.013 with six, whose last
 // sector's long rays start late).  Taking the long rays of a class first keeps the last
@@ -1295,7 +1298,7 @@ inline RayOrder ray_order(const WalkSched& w, int64_t states) {
     RayOrder o;
     const int nq = w.queues;
     o.nq = nq;
-    o.dirs = w.one_mesh && states >= 4 * 256 * (int64_t)w.blocks ? kDirClasses : 1;
+    o.dirs = w.one_mesh && !w.open_mesh && states >= 4 * 256 * (int64_t)w.blocks ? kDirClasses : 1;
     o.sub = kMaxBuckets / (nq * o.dirs * kLenClasses);
     o.nb = nq * o.stride() + 1;
     return o;
@@ -3711,12 +3714,19 @@ hipError_t launch_backward(const DevMesh& M, const BwdArgs& a_in, void* ws, cons
         // that a query's walks stay side by side.  1,048,576 queries on 327,680
         // faces, backward: 2.63 ms (three blocks per CU, refill at 32 idle lanes),
         // 2.26 (four, 32), 2.16 (four, 48), 1.92 (six, 48), 1.79 (six, 63).
+        // Where many walks end at a boundary, waves refilled as a whole wait for the
+        // few that do not (mesh_open; 1,000,000 queries, boundary edges per hundred
+        // faces and ms at 63 idle lanes and 32: 0.4 1.64 and 1.64, 1.1 1.64 and 1.50
+        // on 327,680 faces and 1.09 and 1.08 on 81,920, 3.7 1.11 and 1.00, 15 0.92
+        // and 0.84; 600,000 on a Moebius strip, 1.7, 1.29 and 1.08), except in batches
+        // that hardly refill (100,000: 210 and 222 us)
         int blocks = w.blocks;
         if (gfd && w.own_blocks) {
             const int64_t lanes = (int64_t)per1 * a.n / (256 * (int64_t)w.cus);   // blocks per CU at one state per lane
             blocks = w.cus * (int)std::max<int64_t>(std::min(2, w.gfd_per_cu), std::min<int64_t>(lanes, w.gfd_per_cu));
         }
-        const int refill = gfd && w.own_refill ? 64 - 64 % per1 : w.refill_min;
+        const bool whole = !w.open_mesh || (int64_t)per1 * a.n < 512 * (int64_t)blocks;
+        const int refill = gfd && w.own_refill && whole ? 64 - 64 % per1 : w.refill_min;
         hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, counter);
         SG_DISPATCH(k_walk_bwd, false, flip, dim3((unsigned)blocks), dim3(block), s, M, s1,
                     QueueRanges{cnt, stride, per1}, counter, a.max_steps, a.snap, refill, w.queues);

@@ -82,6 +82,7 @@ struct PackedMesh {
     int64_t n_verts = 0, n_faces = 0;
     double mean_edge = 0.0;
     int64_t n_edges = 0;              // undirected edges
+    int64_t n_boundary = 0;           // boundary edges
     int32_t has_flip = 0;
 };
 
@@ -112,11 +113,18 @@ hipError_t launch_exp_plain(const DevMesh& M, const ExpArgs& a, hipStream_t s);
 
 // Schedule of a persistent walk launch.
 constexpr int kMaxQueues = 64;
+// A ray crosses boundary edges at about 0.7 of their number per face and crossing:
+// from one per hundred faces on, a good part of rays of some 50 crossings and more
+// end early, in no order of their lengths.  The rays of one direction class, and a
+// query's walks, then no longer end together (the walk order, GFD's long walks).
+inline bool mesh_open(int64_t n_boundary, int64_t n_faces) { return 100 * n_boundary >= n_faces; }
+
 struct WalkSched {
     int blocks;       // 256-lane blocks launched
     int refill_min;   // idle lanes (of 64 per ray slot) that trigger a refill
     int queues;       // ray queues: a multiple of 8, at most kMaxQueues
     bool one_mesh;    // the handle holds one mesh (the walk order's direction classes)
+    bool open_mesh;   // many rays end at a boundary (mesh_open)
     // the backward's walks: their own block counts and refill thresholds, or those above
     bool own_blocks, own_refill;
     int cus, gfd_per_cu;   // CUs, and the most blocks of GFD's long-walk pass each holds

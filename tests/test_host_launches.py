@@ -197,3 +197,29 @@ def test_a_failed_allocation_is_reported_once(lib, call):
         lib.L.fake_malloc_limit(2 ** 63)
     assert lib.exp(h, 100, kernel=sg.KERNEL_PLAIN) == 0
     assert run() == 0
+
+
+@pytest.mark.parametrize("kind,open_mesh", [("closed", False), ("one hole", False), ("holes", True), ("mobius", True)])
+def test_schedule_of_meshes_with_boundaries(lib, kind, open_mesh):
+    """Where many rays end at a boundary the walks take one direction class and refill
+    at 32 idle lanes: neither a class's rays nor a query's walks end together there."""
+    X, F = _canonical("mobius" if kind == "mobius" else "icosphere")
+    if kind in ("one hole", "holes"):
+        X, F = M.canonical(*M.remove_faces(*M.icosphere(3), [5] if kind == "one hole" else [0, 97, 194, 291, 388, 485]))
+    h, seen = lib.mesh(X, F), {}
+
+    def launch(name, dev, args):
+        if name == "k_walk_bwd":
+            seen["refill"] = _int(args, 6)
+        if name == "k_walk":   # QueueRanges: the buckets of a range follow its pointer
+            seen["stride"] = C.cast(args[2], C.POINTER(C.c_int32))[2]
+
+    with lib.on_launch(launch):
+        assert lib.exp(h, 800000, kernel=sg.KERNEL_PERSISTENT) == 0   # (four rays per lane and more)
+        assert lib.backward(h, sg.BWD_GFD, 1000) == 0   # (a batch that fits the walk's lanes: whole waves)
+        assert seen["refill"] in (63, 64)
+        assert lib.backward(h, sg.BWD_GFD, 300000) == 0
+        got = dict(seen)
+        assert lib.backward(h, sg.BWD_GFD, 1000, refill_min=17) == 0
+    assert seen["refill"] == 17
+    assert got == dict(refill=32 if open_mesh else 63, stride=1024 if open_mesh else 1008)

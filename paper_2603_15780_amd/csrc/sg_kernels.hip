@@ -891,8 +891,9 @@ SG_HD __forceinline__ void cross_edge(const Exit& x, float len, int32_t nx, uint
     if (kHash) st.hash = fnv_face(st.hash, id);
 }
 
-// A step that reaches the cap, a vertex or the boundary, from its start (the
-// exit is found again: these are a few in a million crossings).
+// A step that reaches the cap or a vertex, or with hole avoidance the boundary,
+// from its start (the exit is found again: on closed meshes these are a few in a
+// million crossings).
 template <bool kHash, bool kFlip, bool kHole>
 SG_HD __forceinline__ int odd_step(const DevMesh& M, Ray& st, int32_t max_steps, float snap, Final& fin) {
     const FaceRec rec = face_rec(M, st.h);
@@ -949,8 +950,10 @@ SG_HD __forceinline__ int odd_step(const DevMesh& M, Ray& st, int32_t max_steps,
     return kStepContinue;
 }
 
-// One geodesic_step: find the exit of the current face, then end in the face
-// or cross into the next chart; everything else is odd_step.  Each outcome
+// One geodesic_step: find the exit of the current face, then end in the face or
+// on a boundary edge, or cross into the next chart; everything else is odd_step
+// (which took boundary edges too: with 4,000 holes in 81,920 faces, where nine rays
+// in ten end at one, 1,400,000 rays 377 us, 304 now).  Each outcome
 // has its own branch and the odd one starts from the unchanged state, so every
 // state word is computed where it lives (merging the outcomes' values instead
 // took 7 to 14 register moves per crossing).
@@ -999,8 +1002,8 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int
     const float Lr = st.Lhi + st.Llo;
     const uint64_t live = lane_mask(alive);
     const uint64_t m_end = lane_mask(!(x.lam < Lr)) & live;   // ends inside this face (ties stay in the face)
-    const uint64_t m_odd = (lane_mask(st.ncross >= max_steps) | lane_mask(x.mu < snap) | lane_mask(x.omu < snap) |
-                            lane_mask(nx < 0)) & ~m_end & live;
+    const uint64_t m_rare = lane_mask(st.ncross >= max_steps) | lane_mask(x.mu < snap) | lane_mask(x.omu < snap);
+    const uint64_t m_odd = (m_rare | lane_mask(nx < 0)) & ~m_end & live;
     if (lane_of(live & ~(m_end | m_odd)))
         cross_edge<kHash, kFlip>(x, len, nx, id, st);
     if constexpr (kLate) q = face_words(face_rec(M, max(nx, 0)));
@@ -1012,7 +1015,10 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int
     if constexpr (kDefer) {
         if (lane_of(m_odd)) ev = kStepOdd;
     } else if (__builtin_expect(m_odd != 0ull, 0)) {
-        if (lane_of(m_odd)) {
+        if (!kHole && lane_of(m_odd & ~m_rare)) {   // on the boundary edge (Sec. 4, original behaviour)
+            set_final(fin, st, fmaf(x.lam, cs, st.s), x.lam * sn, kRayBoundary);
+            ev = kStepDone;
+        } else if (lane_of(m_odd)) {
             ev = odd_step<kHash, kFlip, kHole>(M, st, max_steps, snap, fin);
             if (ev == kStepContinue) q = face_words(face_rec(M, st.h));
         }

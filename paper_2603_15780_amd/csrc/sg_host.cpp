@@ -49,6 +49,7 @@ struct sg_mesh_s {
     int32_t part_face[sg::kParts + 1] = {};
     int32_t has_flip = 0;
     bool open_mesh = false;
+    int32_t park_wait = 0;
     size_t bytes = 0;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timed, spare;   // walk-kernel event pairs
     sg::PackedMesh host;   // face order, mesh offsets and edge count
@@ -72,7 +73,8 @@ struct sg_mesh_s {
         const PiCells& c = pi_cells[cells];
         return sg::PiMesh{d_piface, c.grid, c.start, c.face, n_faces, n_meshes, pi_tie, pi_slack};
     }
-    sg::DevMesh dev(int32_t hole_avoid = 0) const {
+    sg::DevMesh dev(int32_t boundary_mode = SG_BOUNDARY_STOP) const {
+        const int32_t hole_avoid = boundary_mode == SG_BOUNDARY_AVOID ? park_wait : 0;
         sg::DevMesh d{d_face,  d_F,     d_X,     d_half, d_perm,     d_order,
                       n_faces, n_verts, has_flip, {},   d_twin, hole_avoid, reinterpret_cast<const float4*>(d_geo)};
         for (int p = 0; p <= sg::kParts; ++p) d.part_face[p] = part_face[p];
@@ -852,6 +854,7 @@ int sg_mesh_create(const float* X_host, int64_t n_verts, const int32_t* F_host, 
     m->mean_edge = pm.mean_edge;
     m->has_flip = pm.has_flip;
     m->open_mesh = sg::mesh_open(pm.n_boundary, n_faces);
+    m->park_wait = sg::park_wait(pm.n_boundary, n_faces);
     for (int p = 0; p <= sg::kParts; ++p) m->part_face[p] = (int32_t)pm.part_start[p];
     std::vector<int32_t> order32(pm.order.begin(), pm.order.end());
     // corners of each vertex (3 f + k over internal faces), grouped by vertex

@@ -75,7 +75,8 @@ struct DevMesh {
     int32_t has_flip;           // some adjacent faces disagree in orientation (non-orientable or mixed)
     int32_t part_face[kParts + 1]; // face ranges of the parts
     const int32_t* twin;        // [3 n_faces] half-edge on the other side of each edge, -1 on the boundary
-    int32_t hole_avoid;         // per call: 1 = trace along boundaries instead of stopping (Sec. 4)
+    int32_t hole_avoid;         // per call: 0, or trace along boundaries instead of stopping (Sec. 4); a lane with
+                                // such a step then waits this many for others (park_wait)
     const float4* geo;          // [n_faces, 4]: the face's three vertex positions (w: its FaceRec's edge
                                 // lengths l[0..2]), then (c0 bits, c1 bits, user face id bits, 0): one
                                 // 64-byte record per face

@@ -1030,19 +1030,24 @@ SG_HD __forceinline__ int walk_step(const DevMesh& M, FaceWords& q, Ray& st, int
 // looks through vertex fans, some 4 us of dependent loads) and one lane's would
 // hold up its whole wave.  Such a lane is parked instead, and the wave takes the
 // parked lanes together once there are kParkMin of them, the first has waited
-// kParkWait steps, or no other lane can walk on.  200,003 rays on 94,000 faces
+// M.hole_avoid steps, or no other lane can walk on.  200,003 rays on 94,000 faces
 // with holes: 0.95 ms taken at once, 0.47, 0.40, 0.43 and 0.49 ms with 8, 16, 32
-// and 64 lanes.  Where odd steps are rare (a vertex now and then, one hole) a lane
-// that waits for the others to be parked too ends long after them: 300,000 rays
-// on 327,680 faces, one left out, take 517 us without a bound on the wait, 422,
-// 420, 430 and 452 with 32, 48, 64 and 128 steps, 415 if taken at once; those
-// with holes 0.42, 0.40, 0.39 and 0.39 ms.
+// and 64 lanes.
 constexpr int kParkMin = 16;
-constexpr int kParkWait = 48;
 
-SG_HD __forceinline__ bool park_full(uint64_t act, uint64_t park, int& waited) {
+// The limit in a scalar register (left to the compiler it was loaded again at each
+// step: 200,003 rays 401 -> 408 us).
+SG_HD __forceinline__ int park_limit(const DevMesh& M) {
+    int wait = M.hole_avoid;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(wait));
+#endif
+    return wait;
+}
+
+SG_HD __forceinline__ bool park_full(int wait, uint64_t act, uint64_t park, int& waited) {
     waited = park != 0ull ? waited + 1 : 0;
-    return park != 0ull && (__builtin_popcountll(park) >= kParkMin || waited >= kParkWait || (act & ~park) == 0ull);
+    return park != 0ull && (__builtin_popcountll(park) >= kParkMin || waited >= wait || (act & ~park) == 0ull);
 }
 
 template <bool kHash, bool kFlip, bool kHole>
@@ -1051,6 +1056,7 @@ SG_HD __forceinline__ void walk_to_end(const DevMesh& M, Ray& st, int32_t max_st
     if constexpr (kHole) {   // (the lanes that are here, as one wave)
         uint64_t act = lane_mask(true), park = 0ull;
         int waited = 0;
+        const int wait = park_limit(M);
         while (act != 0ull) {
             bool odd = false, done = false;
             if (lane_of(act & ~park)) {
@@ -1059,7 +1065,7 @@ SG_HD __forceinline__ void walk_to_end(const DevMesh& M, Ray& st, int32_t max_st
                 done = ev == kStepDone;
             }
             park |= lane_mask(odd);
-            if (park_full(act, park, waited)) {
+            if (park_full(wait, act, park, waited)) {
                 if (lane_of(park)) {
                     done = odd_step<kHash, kFlip, true>(M, st, max_steps, snap, fin) == kStepDone;
                     if (!done) q = face_words(face_rec(M, st.h));
@@ -1843,6 +1849,7 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
     uint64_t act = 0ull;    // lanes with a ray in flight
     int waited = 0;         // steps since the first was parked
     uint64_t park = 0ull;   // of these, with an odd step to take (kParkMin)
+    const int wait = kHole ? park_limit(M) : 0;
     QueueCursor qc = queue_start(nq);
     int64_t q = 0;
     int32_t ray = 0;   // with fin_out: the query index, carried in the initial state's crossing count
@@ -1908,7 +1915,7 @@ __device__ __forceinline__ void walk_loop(const DevMesh& M, StateRec* states, Qu
                     if (!odd) settle(ev, fin);
                 }
                 park |= lane_mask(odd);
-                if (park_full(act, park, waited)) {
+                if (park_full(wait, act, park, waited)) {
                     if (lane_of(park)) {
                         Final fin;
                         const int ev = odd_step<kHash, kFlip, true>(M, st, max_steps, snap, fin);

@@ -119,6 +119,16 @@ constexpr int kMaxQueues = 64;
 // query's walks, then no longer end together (the walk order, GFD's long walks).
 inline bool mesh_open(int64_t n_boundary, int64_t n_faces) { return 100 * n_boundary >= n_faces; }
 
+// Hole avoidance: the steps that a lane waits at most for others to need an odd step
+// too (meeting a boundary, or now and then a vertex).  Where these are rare it would
+// end long after the others: us with 8, 16, 24 and 48 steps, boundary edges per
+// thousand faces, for 5,000 rays in the plain kernel and 1,000,000 in the persistent:
+// 0.4 on 81,920 faces 85, 86, 92, 104 and 527, 513, 511, 526; 1.1 92, 96, 94, 99 and
+// 543, 535, 541, 545; 3.7 124, 114, 118, 124 and 656, 613, 592, 577; 11 174, 149, 148,
+// 157 and 814, 777, 762, 757; 37 296, 212, 190, 190 and 1,141, 910, 829, 760; without
+// boundaries 100,000 rays on 20,480 faces 48, 48, 49, 57.
+inline int park_wait(int64_t n_boundary, int64_t n_faces) { return 300 * n_boundary >= n_faces ? 48 : 16; }
+
 struct WalkSched {
     int blocks;       // 256-lane blocks launched
     int refill_min;   // idle lanes (of 64 per ray slot) that trigger a refill

@@ -225,12 +225,13 @@ def test_schedule_of_meshes_with_boundaries(lib, kind, open_mesh):
     assert got == dict(refill=32 if open_mesh else 63, stride=1024 if open_mesh else 1008)
 
 
-@pytest.mark.parametrize("kind,wait", [("closed", 16), ("one hole", 16), ("holes", 48)])
+@pytest.mark.parametrize("kind,wait", [("closed", 16), ("one hole", 16), ("holes", 48), ("sheet", 48)])
 def test_wait_of_an_odd_step(lib, kind, wait):
     """With hole avoidance a lane waits for others that meet a boundary: a third as long
     where few do.  (The word behind the mesh's twin pointer; 0 where rays stop.)"""
-    holes = {"closed": [], "one hole": [5], "holes": [0, 97, 194, 291, 388, 485]}[kind]
-    X, F = M.canonical(*(M.remove_faces(*M.icosphere(3), holes) if holes else M.icosphere(3)))
+    holes = {"one hole": [5], "holes": [0, 97, 194, 291, 388, 485]}.get(kind)
+    X, F = M.canonical(*(M.remove_faces(*M.icosphere(3), holes) if holes else
+                         M.mobius_strip(500, 400) if kind == "sheet" else M.icosphere(3)))   # (1,000 of 400,000)
     h, seen = lib.mesh(X, F), []
     with lib.on_launch(lambda name, dev, args: name in ("k_exp_plain", "k_walk") and
                        seen.append(C.cast(args[0] + 112, C.POINTER(C.c_int32))[0]) or 0):

@@ -456,28 +456,42 @@ int build_pi_cells(sg_mesh m, int set) {
     return SG_OK;
 }
 
-// out: the handle's data with the cells for steps of this length
-int ensure_pi(sg_mesh m, double step, sg::PiMesh& out) {
+// out: the handle's data with the cells for steps of this length.  Where these are
+// not built yet and cannot be now (a graph is recorded on the stream, or there is no
+// memory), the other cells do: they give the same results.
+int ensure_pi(sg_mesh m, double step, hipStream_t st, sg::PiMesh& out) {
     std::lock_guard<std::mutex> lock(m->pi_mu);
     auto cells = [&] { return step > kPiLongStep * m->pi_edge ? 1 : 0; };
-    if (m->pi_ext.empty() || !m->pi_cells[cells()].ready) {
+    int use = cells();
+    if (m->pi_ext.empty() || !m->pi_cells[use].ready) {
+        const bool other = m->pi_cells[1 - use].ready;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (other && hipStreamIsCapturing(st, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) {
+            out = m->pi(1 - use);
+            return SG_OK;
+        }
         const OnDevice dev(m->device);
         if (dev.err != hipSuccess) return hip_fail(dev.err, "projection grid");
         int rc = SG_OK;
         try {
             if (m->pi_ext.empty()) rc = build_pi_faces(m);
-            if (rc == SG_OK) rc = build_pi_cells(m, cells());
+            use = cells();
+            if (rc == SG_OK) rc = build_pi_cells(m, use);
         } catch (const std::bad_alloc&) {
             rc = fail(SG_E_OOM, "out of host memory");
         }
-        if (rc != SG_OK) {
-            if (!m->pi_cells[0].ready && !m->pi_cells[1].ready) free_pi(m);
-            else free_pi_cells(m->pi_cells[cells()]);
+        if (rc == SG_OK) {
+            m->pi_cells[use].ready = true;
+        } else if (other) {
+            free_pi_cells(m->pi_cells[use]);
+            if (rc != SG_E_OOM) return rc;
+            use = 1 - use;
+        } else {
+            free_pi(m);
             return rc;
         }
-        m->pi_cells[cells()].ready = true;
     }
-    out = m->pi(cells());
+    out = m->pi(use);
     return SG_OK;
 }
 
@@ -1284,7 +1298,7 @@ int sg_pi_exp(sg_mesh mesh, int64_t n, const int32_t* f, const float* b, const f
     if (!f || !b || !v || !f_out || !b_out || !p_out || !v_out) return fail(SG_E_ARG, "a required array is NULL");
     if (K > 0 && (!W || !W_out)) return fail(SG_E_ARG, "W and W_out are required when K > 0");
     sg::PiMesh P;
-    rc = ensure_pi(mesh, po.step, P);
+    rc = ensure_pi(mesh, po.step, (hipStream_t)stream, P);
     if (rc != SG_OK) return rc;
     sg::PiArgs a{};
     a.n = n;
@@ -1340,7 +1354,7 @@ int sg_pi_backward(sg_mesh mesh, int32_t mode, int64_t n, const int32_t* f, cons
     if (mode == SG_BWD_EP && (!f_out || !v_out)) return fail(SG_E_ARG, "EP needs the forward's f_out and v_out");
     if (n >= ((int64_t)1 << 29)) return fail(SG_E_ARG, "the PI backward takes fewer than 2^29 queries per call");
     sg::PiMesh P;
-    rc = ensure_pi(mesh, po.step, P);
+    rc = ensure_pi(mesh, po.step, (hipStream_t)stream, P);
     if (rc != SG_OK) return rc;
     sg::BwdArgs a{};
     a.n = n;

@@ -15,6 +15,7 @@ typedef int (*LaunchCb)(const char* kernel, int device, void** args);
 LaunchCb g_launch = nullptr;
 size_t g_limit = ~(size_t)0;   // hipMalloc refuses more than this at once
 int g_device = 0;
+bool g_capturing = false;
 hipError_t g_last = hipSuccess;
 struct Config {
     dim3 grid, block;
@@ -41,6 +42,7 @@ char fake_fatbin[64];
 void fake_on_launch(LaunchCb cb) { g_launch = cb; }
 void fake_malloc_limit(size_t n) { g_limit = n; }
 void fake_set_device(int d) { g_device = d; }
+void fake_set_capturing(int on) { g_capturing = on != 0; }   // (synchronous calls then fail)
 int fake_device() { return g_device; }
 
 void** __hipRegisterFatBinary(const void*) {
@@ -100,10 +102,10 @@ hipError_t hipGetSymbolAddress(void** p, const void*) {
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
-    *c = hipStreamCaptureStatusNone;
+    *c = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipMalloc(void** p, size_t n) { return take(p, n); }
+hipError_t hipMalloc(void** p, size_t n) { return g_capturing ? set(hipErrorStreamCaptureUnsupported) : take(p, n); }
 hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) { return take(p, n); }
 hipError_t hipFree(void* p) {
     std::free(p);
@@ -111,6 +113,7 @@ hipError_t hipFree(void* p) {
 }
 hipError_t hipFreeAsync(void* p, hipStream_t) { return hipFree(p); }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+    if (g_capturing) return set(hipErrorStreamCaptureUnsupported);
     std::memcpy(d, s, n);
     return hipSuccess;
 }

@@ -63,3 +63,26 @@ def test_long_steps_cost_no_more_than_wide_cells():
     mesh.pi_exp(*t, step=1.0)
     torch.cuda.synchronize()
     assert time.perf_counter() - t0 < 0.6
+
+
+def test_a_step_not_met_before_in_a_graph():
+    """A call recorded into a graph cannot build a grid: with short steps met before, long
+    ones take their cells, with the same result at every replay."""
+    from paper_2603_15780_amd import sg
+    X, F = M.canonical(*M.icosphere(4))
+    mesh, t = sg.Mesh(X, F), _rays(X, F, 500, 2.0)
+    step = 8.0 * mesh.info()["mean_edge"]
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        mesh.pi_exp(*t, step=0.5 * mesh.info()["mean_edge"])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        out = mesh.pi_exp(*t, step=step, want_steps=True)
+    ref = mesh.pi_exp(*t, step=step, want_steps=True)
+    for _ in range(3):
+        for k in KEYS:
+            out[k].zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        _same(out, ref)

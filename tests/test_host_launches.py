@@ -157,20 +157,21 @@ def test_record_budget_bounds_the_workspace(lib, wide, n, records):
     assert need(records) - need(-1) <= (1 + 8 / 384) * (budget + max(budget, 768 * 196608)) + (4 << 20)
 
 
+def _extents(name, dev, args):
+    """1,280 faces of edge 0.02 in a box of 1, for k_pi_extents."""
+    if name == "k_pi_extents":
+        out = C.cast(args[2], C.POINTER(C.POINTER(C.c_double))).contents
+        for part in range(16):
+            for k, x in enumerate((0.0, 0.0, 0.0, 1.0, 1.0, 1.0, 3 * 1280 * 0.02 / 16, 1.0)):
+                out[8 * part + k] = x
+
+
 @pytest.mark.parametrize("limit,rc", [(1 << 20, 0), (400 << 10, 0), (100 << 10, sg.SG_E_OOM)])
 def test_projection_grid_without_memory_for_fine_cells(lib, limit, rc):
     """1,280 faces of edge 0.02 in a box of 1: 128 cells a face (up to 655 KB) in fine
     cells, 32 (164 KB) in wide ones, which a handle whose fine cells do not fit takes."""
     h = lib.mesh(*_canonical("icosphere"))
-
-    def extents(name, dev, args):
-        if name == "k_pi_extents":
-            out = C.cast(args[2], C.POINTER(C.POINTER(C.c_double))).contents
-            for part in range(16):
-                for k, x in enumerate((0.0, 0.0, 0.0, 1.0, 1.0, 1.0, 3 * 1280 * 0.02 / 16, 1.0)):
-                    out[8 * part + k] = x
-
-    with lib.on_launch(extents):
+    with lib.on_launch(_extents):
         lib.L.fake_malloc_limit(limit)
         try:
             assert lib.pi_exp(h, 100) == rc
@@ -239,3 +240,32 @@ def test_wait_of_an_odd_step(lib, kind, wait):
             for mode in (sg.BOUNDARY_STOP, sg.BOUNDARY_AVOID):
                 assert lib.exp(h, 100, kernel=kernel, boundary_mode=mode) == 0
     assert seen == [0, wait, 0, wait]
+
+
+@pytest.mark.parametrize("first,then", [(0.01, 0.5), (0.5, 0.01)])
+def test_projection_with_the_other_cells(lib, first, then):
+    """Short and long steps (six edges are 0.12) have grids of their own.  A call whose
+    grid is not built yet takes the other's where it cannot build it: while a graph is
+    recorded, and without memory."""
+    h, cells = lib.mesh(*_canonical("icosphere")), []
+
+    def launch(name, dev, args):
+        _extents(name, dev, args)
+        if name == "k_pi_exp_grid":   # PiMesh: the grids' address
+            cells.append(C.cast(args[0], C.POINTER(C.c_uint64))[1])
+
+    with lib.on_launch(launch):
+        assert lib.pi_exp(h, 100, first) == 0
+        lib.L.fake_set_capturing(1)
+        try:
+            assert lib.pi_exp(h, 100, then) == 0 and lib.pi_exp(h, 100, first) == 0
+        finally:
+            lib.L.fake_set_capturing(0)
+        lib.L.fake_malloc_limit(0)
+        try:
+            assert lib.pi_exp(h, 100, then) == 0
+        finally:
+            lib.L.fake_malloc_limit(2 ** 63)
+        assert len(set(cells)) == 1
+        assert lib.pi_exp(h, 100, then) == 0 and lib.pi_exp(h, 100, first) == 0
+    assert cells[-2] != cells[0] == cells[-1]

@@ -68,10 +68,11 @@ struct sg_mesh_s {
     PiCells pi_cells[2];
     std::vector<double> pi_ext;   // the meshes' extents
     double pi_edge = 0.0;         // the smallest mean edge of a mesh
+    int32_t pi_slim = 0;          // some face is slim
     double pi_tie = 0.0, pi_slack = 0.0;
     sg::PiMesh pi(int cells) const {
         const PiCells& c = pi_cells[cells];
-        return sg::PiMesh{d_piface, c.grid, c.start, c.face, n_faces, n_meshes, pi_tie, pi_slack};
+        return sg::PiMesh{d_piface, c.grid, c.start, c.face, n_faces, n_meshes, pi_slim, pi_tie, pi_slack};
     }
     sg::DevMesh dev(int32_t boundary_mode = SG_BOUNDARY_STOP) const {
         const int32_t hole_avoid = boundary_mode == SG_BOUNDARY_AVOID ? park_wait : 0;
@@ -386,7 +387,7 @@ int build_pi_faces(sg_mesh m) {
     const std::vector<int64_t>& fo = m->host.face_off;
     const int nm = (int)fo.size() - 1;
     const sg::DevMesh M = m->dev();
-    std::vector<double> ext((size_t)nm * sg::kPiParts * sg::kPiExtent);
+    std::vector<double> ext((size_t)nm * sg::kPiParts * sg::kPiExtent + 1);   // and the slim word
     const size_t off_bytes = (fo.size() * sizeof(int64_t) + 255) & ~(size_t)255;
     void* tmp = nullptr;
     const size_t face_bytes = (size_t)m->n_faces * sizeof(sg::PiFace);
@@ -396,8 +397,8 @@ int build_pi_faces(sg_mesh m) {
     double* d_ext = reinterpret_cast<double*>(reinterpret_cast<char*>(tmp) + off_bytes);
     e = hipMemcpy(tmp, fo.data(), fo.size() * sizeof(int64_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = sg::launch_pi_extents(M, reinterpret_cast<const int64_t*>(tmp), nm, d_ext, nullptr);
+    if (e == hipSuccess) e = sg::launch_pi_faces(M, m->d_piface, reinterpret_cast<uint32_t*>(d_ext + ext.size() - 1), nullptr);
     if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = sg::launch_pi_faces(M, m->d_piface, nullptr);
     (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "projection grid");
     m->pi_edge = INFINITY;
@@ -406,6 +407,7 @@ int build_pi_faces(sg_mesh m) {
         for (int p = 0; p < sg::kPiParts; ++p) el += ext[((size_t)k * sg::kPiParts + p) * sg::kPiExtent + 6];
         if (fo[k + 1] > fo[k]) m->pi_edge = std::min(m->pi_edge, el / (3.0 * (double)(fo[k + 1] - fo[k])));
     }
+    std::memcpy(&m->pi_slim, &ext.back(), sizeof m->pi_slim);
     m->pi_ext = std::move(ext);
     return SG_OK;
 }

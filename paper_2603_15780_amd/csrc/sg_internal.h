@@ -89,7 +89,7 @@ struct DevMesh {
 // the unit normal in float64.
 struct alignas(16) PiFace {
     float x0[3], x1[3], x2[3];
-    float pad;
+    float slim;   // 1: too slim for the search's cheap distance, else 0
     double n[3];
 };
 static_assert(sizeof(PiFace) == 64, "PiFace is one 64-byte segment");
@@ -117,6 +117,7 @@ struct PiMesh {
     const int32_t* cell_face;  // user face ids
     int64_t n_faces;
     int32_t n_meshes;
+    int32_t slim;              // some face is PiFace::slim
     double tie;                // distances within tie of the smallest are a tie (a shared nearest point)
     double slack;              // extra reach of the cell search over the tie (rounding of box distances)
 };

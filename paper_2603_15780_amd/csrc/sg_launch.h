@@ -197,15 +197,15 @@ size_t pi_order_workspace(int64_t n);
 hipError_t launch_pi_exp(const PiMesh& P, const DevMesh& M, const PiArgs& a, void* ws, hipStream_t s);
 // The projection data of a handle, in five parts.  Extents: kPiParts partial
 // results per mesh (lowest and highest coordinates, sum of edge lengths, largest
-// absolute coordinate of a share of all vertices).  The face records.  The
-// numbers of cell entries that a choice of grids takes, and of faces with very many
-// (sum[0], sum[1]; counting lists the latter in large, 1 + n_large words).  Counts: at cells[c] the
-// entries before cell c (cells[total]: all of them; tile: scan_tiles(total + 1)
-// words).  Fill: the entries; cells[c] moves to the end of cell c, so that
+// absolute coordinate of a share of all vertices).  The face records (slim: whether
+// one of them is).  The numbers of cell entries that a choice of grids takes, and of
+// faces with very many (sum[0], sum[1]; counting lists the latter in large, 1 +
+// n_large words).  Counts: at cells[c] the entries before cell c (cells[total]: all
+// of them; tile: scan_tiles(total + 1) words).  Fill: the entries; cells[c] moves to the end of cell c, so that
 // cells - 1 (a zero word) are the cells' starts.
 constexpr int kPiParts = 16, kPiExtent = 8;
 hipError_t launch_pi_extents(const DevMesh& M, const int64_t* face_off, int n_meshes, double* out, hipStream_t s);
-hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, hipStream_t s);
+hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, uint32_t* slim, hipStream_t s);
 hipError_t launch_pi_entries(const PiMesh& P, unsigned long long* sum, double pad, hipStream_t s);
 hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, double pad, uint32_t* tile, uint32_t* large,
                            int64_t n_large, hipStream_t s);

@@ -208,14 +208,15 @@ __device__ __forceinline__ PiHit project_grid(const PiMesh& P, const PiGrid& G, 
     return hit;
 }
 
-// Squared distance of q to face F, with approximate reciprocals and without
-// face_closest's square roots and branches.  det is the squared sine of a corner
-// times g11 g22 and comes with an error of 2^-52 g11 g22, so below kPiSlim g11 g22
-// the inside test and the distance are taken the way face_closest takes them
-// (what the solve leaves of w, not height^2 / det: on faces 1e-5 of their length
-// wide that put one query in 35 on another face than the scan's).  Above it
-// height^2 / det is good to 2^-32, and the solve's own error along the face,
-// 2^-32 of |w|, counts squared.  For all faces the form below costs 1% of a call.
+// Squared distance of q to a face that is not slim, with approximate reciprocals
+// and without face_closest's square roots and branches.  det is the squared sine
+// of a corner times g11 g22 and comes with an error of 2^-52 g11 g22, so from
+// kPiSlim g11 g22 on height^2 / det is good to 2^-32, and the solve's own error
+// along the face, 2^-32 of |w|, counts squared.  Slimmer faces (PiFace::slim) take
+// face_closest itself: on faces 1e-5 of their length wide height^2 / det put one
+// query in 35 on another face than the scan's.  A mesh that has such faces has a
+// kernel of its own (kSlim): the look at each face cost meshes without them 1.1 to
+// 2.6% of 1,724 rays on 327,680 faces, whose waves wait for their own results.
 constexpr double kPiSlim = 0x1p-20;
 __device__ __forceinline__ double rcp_near(double x) {   // two Newton steps on the hardware's estimate
     double r = __builtin_amdgcn_rcp(x);
@@ -232,18 +233,11 @@ __device__ __forceinline__ double face_dist2(D3 x0, D3 x1, D3 x2, D3 q) {
     const double g11 = ddot(e1, e1), g12 = ddot(e1, e2), g22 = ddot(e2, e2), r1 = ddot(w, e1), r2 = ddot(w, e2);
     const double det = fma(g11, g22, -g12 * g12), U = fma(g22, r1, -g12 * r2), V = fma(g11, r2, -g12 * r1);
     const double h = ddot(w, dcrs(e1, e2));
-    double dp = h * h * rcp_near(det);
+    const double dp = h * h * rcp_near(det);
     const D3 e3 = dsub(e2, e1), w1 = dsub(w, e1);
     const double d1 = edge_dist2(w, e1, r1, g11), d2 = edge_dist2(w, e2, r2, g22),
                  d3 = edge_dist2(w1, e3, ddot(w1, e3), ddot(e3, e3));
-    bool inside = U >= 0.0 && V >= 0.0 && U + V <= det;
-    if (__builtin_expect(!(det > kPiSlim * (g11 * g22)), 0)) {
-        const double u = U / det, v = V / det;
-        const D3 in = daxpy(-v, e2, daxpy(-u, e1, w));
-        inside = u >= 0.0 && v >= 0.0 && u + v <= 1.0;   // (a determinant of 0: never, and the edges, as there)
-        dp = ddot(in, in);
-    }
-    return inside ? dp : fmin(d1, fmin(d2, d3));
+    return U >= 0.0 && V >= 0.0 && U + V <= det ? dp : fmin(d1, fmin(d2, d3));
 }
 
 // The faces that can be nearest to q, or tie with it, go to the lane's column
@@ -259,6 +253,7 @@ constexpr int kPiCand = 8;
 constexpr int kPiAhead = 4;   // 1,000 rays on 327,680 faces: 1.63 ms with one record in flight, 1.01 with four
 constexpr int kPiBlock = 256;
 
+template <bool kSlim>
 __device__ __forceinline__ int near_faces(const PiMesh& P, const PiGrid& G, D3 q, int32_t (*cand)[kPiBlock]) {
     const int t = (int)threadIdx.x;
     const double h = G.h, m = 16.0 * P.tie, pad = m * m * 1048577.0, grow = 1.0 + 0x1p-20;
@@ -266,13 +261,29 @@ __device__ __forceinline__ int near_faces(const PiMesh& P, const PiGrid& G, D3 q
     double best = __builtin_inf();
     int cnt = 0;
     bool over = false;
+    auto meet = [&](int32_t f, double d2) {
+        if (d2 <= fma(best, grow, pad)) {
+            if (fma(d2, grow, pad) < best) {   // every face so far is farther
+                cnt = 0;
+                over = false;
+            }
+            bool listed = false;   // (a face is in every cell that it comes near)
+            for (int i = 0; i < cnt; ++i) listed |= cand[i][t] == f;
+            if (listed) return;
+            if (cnt < kPiCand) cand[cnt++][t] = f;
+            else over = true;
+            best = fmin(best, d2);
+        }
+    };
     auto cell = [&](int ix, int iy, int iz) {
         const uint32_t c = G.cell0 + (uint32_t)((iz * G.ny + iy) * G.nx + ix);
-        const uint32_t j1 = P.cell_start[c + 1];
-        for (uint32_t j = P.cell_start[c]; j < j1; j += kPiAhead) {
+        const uint32_t j0 = P.cell_start[c], j1 = P.cell_start[c + 1];
+        bool slim = false;
+        for (uint32_t j = j0; j < j1; j += kPiAhead) {
             // kPiAhead faces' records in flight (past the end: the last one's, not tested)
             int32_t fid[kPiAhead];
-            float x[kPiAhead][9];
+            constexpr int kWords = kSlim ? 10 : 9;   // the vertices, and the slim flag
+            float x[kPiAhead][kWords];
 #pragma unroll
             for (int k = 0; k < kPiAhead; ++k) fid[k] = P.cell_face[min(j + (uint32_t)k, j1 - 1u)];
 #pragma unroll
@@ -280,20 +291,20 @@ __device__ __forceinline__ int near_faces(const PiMesh& P, const PiGrid& G, D3 q
 #pragma unroll
             for (int k = 0; k < kPiAhead; ++k) {
                 const double d2 = face_dist2(ld(x[k]), ld(x[k] + 3), ld(x[k] + 6), q);
-                if (j + (uint32_t)k < j1 && d2 <= fma(best, grow, pad)) {
-                    if (fma(d2, grow, pad) < best) {   // every face so far is farther
-                        cnt = 0;
-                        over = false;
-                    }
-                    bool listed = false;   // (a face is in every cell that it comes near)
-                    for (int i = 0; i < cnt; ++i) listed |= cand[i][t] == fid[k];
-                    if (listed) continue;
-                    if (cnt < kPiCand) cand[cnt++][t] = fid[k];
-                    else over = true;
-                    best = fmin(best, d2);
-                }
+                const bool skip = kSlim && x[k][kWords - 1] != 0.f;
+                slim |= skip;
+                if (j + (uint32_t)k < j1 && !skip) meet(fid[k], d2);
             }
         }
+        if (kSlim && slim)
+            for (uint32_t j = j0; j < j1; ++j) {
+                const int32_t f = P.cell_face[j];
+                if (P.face[f].slim == 0.f) continue;
+                D3 p;
+                double b0, b1, b2;
+                const double d = face_closest(P.face[f], q, p, b0, b1, b2);
+                meet(f, d * d);
+            }
     };
     cell(cx, cy, cz);
     auto radius = [&]() { return sqrt(best) * grow + m + P.slack; };
@@ -318,8 +329,9 @@ __device__ __forceinline__ int near_faces(const PiMesh& P, const PiGrid& G, D3 q
 // grid with face_closest, 27 cell boxes tested in each, took 11.7 ms for these
 // on 327,680 faces; with the candidates 3.51 ms, with cells of one edge 2.73,
 // in a spatial order 2.10, with cells of 0.65 edges 1.52.
+template <bool kSlim>
 __device__ __forceinline__ PiHit project_near(const PiMesh& P, const PiGrid& G, D3 q, int32_t (*cand)[kPiBlock]) {
-    const int cnt = near_faces(P, G, q, cand);
+    const int cnt = near_faces<kSlim>(P, G, q, cand);
     if (cnt < 0) return project_grid(P, G, q);
     const int t = (int)threadIdx.x;
     PiHit hit;
@@ -477,7 +489,7 @@ __device__ __forceinline__ void pi_write(const PiArgsT<T>& a, int64_t i, const P
 }
 
 // Grid search: each lane runs its ray to the end.
-template <class T>
+template <class T, bool kSlim>
 __global__ __launch_bounds__(kPiBlock) void k_pi_exp_grid(PiMesh P, PiArgsT<T> a) {
     __shared__ int32_t cand[kPiCand][kPiBlock];
     // ordered rays: the blocks of an XCD (block b runs on XCD b % 8) take one stretch of the order
@@ -498,7 +510,7 @@ __global__ __launch_bounds__(kPiBlock) void k_pi_exp_grid(PiMesh P, PiArgsT<T> a
             status = kRayMaxSteps;
             break;
         }
-        const PiHit h = project_near(P, G, daxpy(a.step, r.v, r.p), cand);
+        const PiHit h = project_near<kSlim>(P, G, daxpy(a.step, r.v, r.p), cand);
         if (h.f < 0) {   // no face within reach (not for a mesh with faces)
             status = kRayBadInput;
             break;
@@ -629,7 +641,7 @@ __global__ __launch_bounds__(256) void k_pi_extents(DevMesh M, const int64_t* fa
     if (t < kPiExtent) out[kPiExtent * (int64_t)blockIdx.x + t] = red[t][0];
 }
 
-__global__ __launch_bounds__(256) void k_pi_faces(DevMesh M, PiFace* face) {
+__global__ __launch_bounds__(256) void k_pi_faces(DevMesh M, PiFace* face, uint32_t* slim) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= M.n_faces) return;
     const int64_t f = M.perm[u];
@@ -639,8 +651,10 @@ __global__ __launch_bounds__(256) void k_pi_faces(DevMesh M, PiFace* face) {
         F.x1[c] = M.X[3 * (int64_t)M.F[3 * f + 1] + c];
         F.x2[c] = M.X[3 * (int64_t)M.F[3 * f + 2] + c];
     }
-    F.pad = 0.f;
     const D3 x0 = ld(F.x0), a = dsub(ld(F.x1), x0), b = dsub(ld(F.x2), x0);
+    const double gaa = ddot(a, a), gab = ddot(a, b), gbb = ddot(b, b);   // (as face_dist2 forms them)
+    F.slim = fma(gaa, gbb, -gab * gab) > kPiSlim * (gaa * gbb) ? 0.f : 1.f;
+    if (F.slim != 0.f) *slim = 1u;
     const D3 c = d3(a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x);
     const double ic = 1.0 / sqrt(c.x * c.x + c.y * c.y + c.z * c.z);
     F.n[0] = c.x * ic;
@@ -783,7 +797,8 @@ hipError_t launch_pi(const PiMesh& P, const PiArgsT<T>& a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
     const dim3 grid((unsigned)((a.n + 255) / 256)), block(256);
     if (a.scan) hipLaunchKernelGGL(k_pi_exp_scan<T>, grid, block, 0, s, P, a);
-    else hipLaunchKernelGGL(k_pi_exp_grid<T>, grid, block, 0, s, P, a);
+    else if (P.slim) hipLaunchKernelGGL((k_pi_exp_grid<T, true>), grid, block, 0, s, P, a);
+    else hipLaunchKernelGGL((k_pi_exp_grid<T, false>), grid, block, 0, s, P, a);
     return hipGetLastError();
 }
 
@@ -993,8 +1008,9 @@ hipError_t launch_pi_extents(const DevMesh& M, const int64_t* face_off, int n_me
     return hipGetLastError();
 }
 
-hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, hipStream_t s) {
-    hipLaunchKernelGGL(k_pi_faces, dim3((unsigned)((M.n_faces + 255) / 256)), dim3(256), 0, s, M, face);
+hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, uint32_t* slim, hipStream_t s) {
+    hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, slim, (int64_t)2);
+    hipLaunchKernelGGL(k_pi_faces, dim3((unsigned)((M.n_faces + 255) / 256)), dim3(256), 0, s, M, face, slim);
     return hipGetLastError();
 }
 

@@ -32,8 +32,13 @@ def _tube(w):     # a closed ring of 64 strips
     return _strips(2 * np.pi * np.arange(64) / 64, 64 * w / (2 * np.pi), True)
 
 
+def _mixed(w):    # the ring beside faces that are not slim
+    (X, F), (Y, G) = M.icosphere(3), _tube(w)
+    return M.canonical(np.concatenate([0.3 * X + [0.35, 0.5, 0.0], Y]), np.concatenate([F, G + X.shape[0]]))
+
+
 @pytest.mark.parametrize("width", [1e-3, 1e-4, 3e-5, 1e-5, 3e-6, 1e-6])
-@pytest.mark.parametrize("mesh", [_fillet, _tube])
+@pytest.mark.parametrize("mesh", [_fillet, _tube, _mixed])
 def test_search_equals_scan_on_needles(mesh, width):
     from paper_2603_15780_amd import sg
     X, F = mesh(width)

@@ -73,7 +73,9 @@ enum {
 enum {
     SG_KERNEL_AUTO = 0,         /* forward: SG_KERNEL_PLAIN when n fits the persistent walk's resident lanes
                                    (walk_blocks x 256 x rays_per_lane, 196,608 by default on 256 CUs), else
-                                   SG_KERNEL_PERSISTENT; the backward's walks are always persistent */
+                                   SG_KERNEL_PERSISTENT; the backward's walks are always persistent.  Right for
+                                   large meshes: below some 300,000 faces the plain kernel is the faster one for
+                                   larger batches too (sg_autotune tries both) */
     SG_KERNEL_PLAIN = 1,        /* one ray per lane, run to completion (Alg. gpu_parallel) */
     SG_KERNEL_PERSISTENT = 2,   /* persistent waves refilled from ray queues (a share per XCD) */
     SG_KERNEL_PARTITIONED = 3   /* the mesh cut into 8 spatial parts, one per XCD: the walk runs in rounds (one
@@ -94,7 +96,9 @@ typedef struct {
     int32_t refill_min;    /* persistent kernel: a wave refetches rays once this many of its 64 lanes are
                               idle (of 128 ray slots with two rays per lane); <= 0: 48 per 64 slots in
                               the forward, 32 in the backward's walks (GFD's long walks: whole waves, the
-                              vertex gradient: 48) */
+                              vertex gradient: 48; on meshes with a boundary edge per hundred faces and
+                              more, GFD's long walks 32).  The backward and the partitioned kernel hold 64
+                              rays a wave whatever rays_per_lane and take more than 64 as 64 */
     int32_t walk_blocks;   /* persistent kernel: 256-lane blocks launched; <= 0: three per CU (GFD's long walks:
                               as many as fit; the vertex gradient: one to three by the batch) */
     int32_t rays_per_lane; /* persistent kernel: rays each lane walks at once, 1 or 2; <= 0: tuned default */
@@ -143,9 +147,11 @@ void sg_mesh_destroy(sg_mesh mesh);
  * for optimisation loops over X (the vertex gradient of sg_exp_backward is
  * their gradient).  X_host [n_verts,3] float32 host, n_verts as at creation.
  * Re-packs the position-dependent parts in float64 on the device (edge lengths,
- * corner angles, vertex total angles, positions, mean edge); the first call
+ * corner angles, vertex total angles, positions, mean edge): the records of a
+ * handle created from these positions, up to one unit (2 pi / 2^32) of a corner
+ * whose angle the device's atan2 rounds another way; the first call
  * allocates room for the new positions, kept by the handle; adjacency, face
- * order and the handle stay.  Synchronous: it waits for the
+ * order and the handle stay.  Synchronous: it waits for the mesh's
  * device to be idle first, since no call may read the mesh while it changes.
  * A zero-area face or a non-finite position returns SG_E_DEGENERATE /
  * SG_E_ARG and leaves the mesh unchanged.
@@ -237,6 +243,10 @@ int sg_exp_transport_noalloc(sg_mesh mesh, int64_t n, const int32_t* f, const fl
  *        given, on meshes whose faces agree in orientation, the base
  *        geodesic's end is taken from them (Appendix "Speed-up GFD and EP
  *        through batching": Exp(p, v) is the forward's) and six are walked.
+ *        With status given too, the end frame that turns g_v and g_W
+ *        (sg_exp_backward_transport) back comes from the saved direction and is
+ *        off by up to 3e-3 where that lies in the lower half plane of the end
+ *        face's first edge; a call without the saved outputs is not.
  *        |v_t| = 0 takes e_par = e_u (the start face's x1 - x0 direction).
  *   grad_X (an extension; the paper has no vertex gradient): the exact
  *        derivative of p' = H_m o ... o H_1(p + v_t), the composition of the
@@ -316,20 +326,31 @@ int sg_backward_workspace_size(sg_mesh mesh, int32_t mode, int64_t n, int32_t wa
  * face's plane, as for sg_exp; the loop runs while the traced length is
  * short of |v_t| (the last step is not clamped, as printed); the nearest
  * point is the minimiser of the distance to each closed triangle over the
- * ray's own mesh, ties (distances within 2^-20 of the largest coordinate,
- * i.e. float32 rounding: a nearest point on an edge or vertex) going to the
- * face whose normal is most nearly parallel to q - p', then the smallest
- * face id; parallel normals leave v unchanged.
- *   search SG_PI_GRID (default): a uniform grid per mesh, cells visited in
- *     rings and skipped when farther than the best distance found, which
+ * ray's own mesh, ties (distances within 1e-12 of the largest coordinate: a
+ * nearest point on an edge or vertex) going to the face whose normal is most
+ * nearly parallel to q - p', then the smallest face id; parallel normals leave
+ * v unchanged.
+ *   search SG_PI_GRID (default): a uniform grid per mesh.  The faces listed in
+ *     the query's own cell are filtered by a cheap distance and settle it while
+ *     the nearest is well inside the cell's reach; else the cells around it
+ *     follow in rings, those farther than the best distance skipped.  It
  *     selects what a scan of every face selects;
  *   search SG_PI_SCAN: the printed scan of every face of the mesh per step.
  * In/out arrays as for sg_exp_transport (K extra vectors keep their angle to
  * v); n_steps[n] int32 (nullable) receives the projection steps taken.
  * status: SG_RAY_OK, SG_RAY_MAXSTEPS (l still short after max_steps steps),
- * SG_RAY_BADINPUT.  The first PI call on a handle, and the first after
- * sg_mesh_update_vertices, builds the per-face records and grids on the device
- * (synchronous; about 100 bytes per face plus 4 bytes per cell).  Float32 arithmetic; the traced length is summed in float-float.
+ * SG_RAY_BADINPUT.  Float64 arithmetic; inputs and outputs are float32.
+ * The first PI call on a handle, and the first after sg_mesh_update_vertices,
+ * builds the per-face records (64 bytes each) and the grids on the device
+ * (synchronous).  A grid takes 4 bytes per cell and 4 per entry of a cell's
+ * list: on a smooth mesh some 12 entries per face and no more cells than 128 per
+ * face, in cells of 0.65 mean edges; wider cells where faces would fill more than
+ * 64 each, or where there is no memory.  Steps of more than six mean edges (of
+ * the mesh of the handle with the shortest) have a grid of their own, in cells of
+ * 1.5 edges, built by the first call that makes them.
+ * A grid search of 65,536 rays and more on 65,536 faces and more takes a
+ * stream-ordered allocation of 8 bytes per ray, in which it orders them; without
+ * memory for it, and while a graph is recorded, it takes them as they come.
  */
 enum { SG_PI_GRID = 0, SG_PI_SCAN = 1 };
 typedef struct {
@@ -367,8 +388,9 @@ int sg_pi_backward_workspace_size(sg_mesh mesh, int32_t mode, int64_t n, size_t*
  * for the plain kernel and for the persistent kernel over rays per lane,
  * refill thresholds (the compaction period), resident blocks per CU (waves
  * per SIMD) and ray queues, then writes the fastest kernel, rays_per_lane,
- * refill_min,
- * walk_blocks, ray_queues into *opts (its other fields are kept and used).
+ * refill_min, walk_blocks, ray_queues into *opts (its other fields are kept and
+ * used).  These are forward picks: in a backward call refill_min and walk_blocks
+ * take the place of its own schedules (leave them 0 there).
  * Synchronizes `stream`; allocates and frees its own scratch outputs and
  * workspace (before any timing).  Not capturable.  *best_ms (nullable)
  * receives the winner's time per call.

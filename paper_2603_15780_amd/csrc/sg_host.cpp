@@ -235,15 +235,19 @@ int check_opts(const sg_opts* in, sg_opts& o, const sg_mesh_s* m, int64_t n = -1
     if (o.ray_queues % 8 != 0 || o.ray_queues > sg::kMaxQueues)
         return fail(SG_E_ARG, "ray_queues must be a multiple of 8, at most %d", sg::kMaxQueues);
     // default schedule: three resident 256-lane blocks per CU, refill at 48 idle lanes (the
-    // fastest in sweeps of 32-60 on 1M, 5.6M and 16.8M rays; the backward keeps 32)
+    // fastest in sweeps of 32-60 on 1M, 5.6M and 16.8M rays; the backward: check_bwd_opts)
     if (o.walk_blocks <= 0)
         o.walk_blocks = m->cu_count * std::min(3, o.kernel == SG_KERNEL_PARTITIONED ? m->part_blocks_per_cu
                                                                                    : m->walk_blocks_per_cu);
     // SG_KERNEL_AUTO: a forward batch (n >= 0) that fits the persistent walk's
     // resident lanes takes the plain kernel: every ray starts at once either way,
-    // so the ordering passes and the queues only add time (65,536 rays on the
-    // 327,680-face mesh: 0.255 against 0.326 ms); larger batches and every
-    // other caller (n < 0) take the persistent walk
+    // so the ordering passes and the queues only add time; larger batches and every
+    // other caller (n < 0) take the persistent walk.  The line is right for large
+    // meshes only (plain and persistent, us, rays of length up to pi / 2): on 327,680
+    // faces 172 and 239 for 65,536 rays, 300 and 317 for 196,608, 533 and 380 for
+    // 300,000; on 1,310,720 faces 810 and 737 for 196,608.  Shorter walks leave the
+    // ordering passes unpaid: on 81,920 faces 183 and 213 for 300,000, 500 and 511 for
+    // 1,048,576, on 1,280 32 and 109, 87 and 193
     if (o.kernel == SG_KERNEL_AUTO)
         o.kernel = n >= 0 && n <= (int64_t)o.walk_blocks * 256 * o.rays_per_lane ? SG_KERNEL_PLAIN
                                                                                : SG_KERNEL_PERSISTENT;
@@ -286,8 +290,9 @@ hipError_t give_workspace(Workspace& w, hipStream_t st) {
 
 // The backward always runs the persistent walk: a partitioned choice of
 // kernel takes the persistent walk's block count.  Its walks refill at 32 idle
-// lanes by default (the forward's 48 made the finite-difference passes, whose
-// queues interleave several walks per query, 3.3 -> 3.9 ms on 1M queries).
+// lanes, except by their own defaults (launch_backward) GFD's long walks, as whole
+// waves, and the vertex gradient's, at 48.  A refill_min or walk_blocks of the
+// caller's, the autotuner's picks among them, takes the place of all of these.
 int check_bwd_opts(const sg_opts* in, sg_opts& o, sg_mesh m) {
     const int rc = check_opts(in, o, m);
     if (rc == SG_OK && o.kernel == SG_KERNEL_PARTITIONED) o.walk_blocks = m->cu_count * m->walk_blocks_per_cu;

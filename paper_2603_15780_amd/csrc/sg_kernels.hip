@@ -2594,6 +2594,9 @@ SG_HD __forceinline__ float3 final_offset(const DevMesh& M, const Final& fin, fl
 }
 
 // Tangent and orientation-consistent normal at the end of a walk.
+// (The sine is fitted to [0, pi], where a walk leaves its angle.  saved_final's lies
+// anywhere, and past pi the frame is off by up to 3e-3: GFD's gradients of g_v and
+// g_W with all saved outputs given.)
 SG_HD __forceinline__ void final_frame(const DevMesh& M, const Final& fin, float3& d3, float3& n3) {
     const int32_t fe = he_face(fin.h);
     const int ke = he_k(fin.h);
@@ -3233,7 +3236,9 @@ __global__ __launch_bounds__(256) void k_gradx_vertices(DevMesh M, BwdArgs a, co
 // The position-dependent parts of a packed mesh from new positions, as the
 // host packer forms them at creation: float64 throughout, rounded once, every
 // product and sum on its own (no fused multiply-add), so that an updated handle
-// holds the records of one created from the same positions.  On one host core
+// holds the records of one created from the same positions, up to one unit of the
+// fixed-point corners: the two atan2 may differ in their last bit, which a corner
+// within 1e-7 of a unit of a rounding boundary shows.  On one host core
 // an update, a forward and a vertex gradient of 131,072 queries on 81,920 faces
 // took 4.07 ms, 1.02 ms with the packing here: 0.1 GB of traffic per million
 // faces in three short kernels, about as long as the copy of the positions.

@@ -268,7 +268,7 @@ class Mesh:
                 hash=torch.empty(n, dtype=torch.int64, device=dev) if want_hash else None,
             )
         ws = None   # (held until the launches are queued)
-        # (a small batch takes the plain kernel, which needs none: no query in its 16 us)
+        # (by default up to 65,536 rays and more take the plain kernel, which needs none: no size query in their 16 us)
         if not noalloc and (n > 65536 or o.kernel != KERNEL_AUTO):
             o, ws = _with_workspace(o, self.exp_workspace_size(n, K, o), dev)
         call = lib().sg_exp_transport_noalloc if noalloc else lib().sg_exp_transport

@@ -67,7 +67,7 @@ struct sg_mesh_s {
     sg::PiFace* d_piface = nullptr;
     PiCells pi_cells[2];
     std::vector<double> pi_ext;   // the meshes' extents
-    double pi_edge = 0.0;         // the smallest mean edge of a mesh
+    double pi_long = 0.0;         // steps longer than this take the coarse cells
     int32_t pi_slim = 0;          // some face is slim
     double pi_tie = 0.0, pi_slack = 0.0;
     sg::PiMesh pi(int cells) const {
@@ -373,20 +373,22 @@ uint64_t pi_grids(const std::vector<int64_t>& fo, const std::vector<double>& ext
 // The projection-integration data of a handle, built on the device: per-face
 // records in user order and, per mesh, uniform grids whose cells list the faces
 // whose bounding boxes, widened by a margin, meet them.
-// Steps of up to kPiLongStep mean edges take cells of 0.65 mean edges: a smooth
-// mesh's query then tests 6 faces instead of 11 with one edge and 18 with 1.5
-// (131,072 rays on 327,680 faces: 1.52, 2.11 and 3.65 ms).  A mesh whose faces
-// differ so much in size that they meet kPiEntries cells each gets wider ones, up
-// to 1.5 edges.  Longer steps leave the surface by many cells, and a query looks
-// through some (2 d / cell)^3 of them d away from it: they take cells of 1.5 edges.
-// 2,048 rays, ms with cells of 0.65 and 1.5 edges: on 20,480 faces, steps of 1.7
-// edges 2.8 and 3.6, of 2.9 5.2 and 4.1, of 5.8 34 and 14, of 29 1,892 and 260; on
-// 81,920 faces 3.5 edges 2.7 and 3.0, 5.8 4.2 and 4.2, 12 37 and 13; on 327,680
-// faces 12 edges 1.9 and 2.8, 23 9.1 and 4.1; on a rough mesh of 81,920 faces 1.7
-// edges 15 and 20, 3.5 21 and 19, 5.8 31 and 21.
+// Short steps take cells of 0.65 mean edges: a smooth mesh's query then tests 6
+// faces instead of 11 with one edge and 18 with 1.5 (131,072 rays on 327,680 faces:
+// 1.52, 2.11 and 3.65 ms).  A mesh whose faces differ so much in size that they meet
+// kPiEntries cells each gets wider ones, up to 1.5 edges.  Long steps leave the
+// surface by many cells, and a query d away from it looks through some (2 d / cell)^3:
+// they take cells of 1.5 edges.  A step s on a surface of radius R ends s^2 / 2 R
+// away, and the line lies at kPiLongStep edges of that, with half a mesh's largest
+// extent for R (the smallest step of a handle's meshes).  ms with cells of 0.65 and
+// 1.5 edges and s^2 / 2 R in edges, 20,000 rays on spheres: 20,480 faces 0.16 1.3 and
+// 2.2, 0.28 2.6 and 2.0, 0.43 5.4 and 2.1, 1.1 21 and 9; 81,920 0.31 1.7 and 2.5,
+// 0.55 3.9 and 2.3; 327,680 0.43 1.6 and 2.2, 0.62 1.5 and 2.5, 1.1 3.2 and 2.4, 2.5
+// 12 and 5.0; 1,310,720 0.31 0.29 and 0.32, 0.55 0.82 and 0.30; in steps of the
+// radius, on 20,480 faces, 1,892 and 260.
 // Called with pi_mu held; on failure the caller frees what was allocated.
 constexpr uint64_t kPiEntries = 64;   // (a smooth mesh: 12)
-constexpr double kPiLongStep = 6.0;
+constexpr double kPiLongStep = 0.4;
 
 int build_pi_faces(sg_mesh m) {
     const std::vector<int64_t>& fo = m->host.face_off;
@@ -406,11 +408,21 @@ int build_pi_faces(sg_mesh m) {
     if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
     (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "projection grid");
-    m->pi_edge = INFINITY;
+    m->pi_long = INFINITY;
     for (int k = 0; k < nm; ++k) {
-        double el = 0.0;
-        for (int p = 0; p < sg::kPiParts; ++p) el += ext[((size_t)k * sg::kPiParts + p) * sg::kPiExtent + 6];
-        if (fo[k + 1] > fo[k]) m->pi_edge = std::min(m->pi_edge, el / (3.0 * (double)(fo[k + 1] - fo[k])));
+        if (fo[k + 1] == fo[k]) continue;
+        double size = 0.0, el = 0.0;
+        for (int c = 0; c < 3; ++c) {
+            double mn = INFINITY, mx = -INFINITY;
+            for (int p = 0; p < sg::kPiParts; ++p) {
+                const double* v = &ext[((size_t)k * sg::kPiParts + p) * sg::kPiExtent];
+                mn = std::min(mn, v[c]);
+                mx = std::max(mx, v[3 + c]);
+                if (c == 0) el += v[6];
+            }
+            size = std::max(size, mx - mn);
+        }
+        m->pi_long = std::min(m->pi_long, std::sqrt(kPiLongStep * size * el / (3.0 * (double)(fo[k + 1] - fo[k]))));
     }
     std::memcpy(&m->pi_slim, &ext.back(), sizeof m->pi_slim);
     m->pi_ext = std::move(ext);
@@ -468,7 +480,7 @@ int build_pi_cells(sg_mesh m, int set) {
 // memory), the other cells do: they give the same results.
 int ensure_pi(sg_mesh m, double step, hipStream_t st, sg::PiMesh& out) {
     std::lock_guard<std::mutex> lock(m->pi_mu);
-    auto cells = [&] { return step > kPiLongStep * m->pi_edge ? 1 : 0; };
+    auto cells = [&] { return step > m->pi_long ? 1 : 0; };
     int use = cells();
     if (m->pi_ext.empty() || !m->pi_cells[use].ready) {
         const bool other = m->pi_cells[1 - use].ready;

@@ -1,4 +1,4 @@
-"""Steps of many edges take a grid of wider cells: the same result as the scan on both
+"""Steps that leave the surface by many cells take a grid of wider cells: the same result as the scan on both
 sides of the line, in any order of calls on a handle, and no slower than short cells."""
 import time
 
@@ -25,7 +25,7 @@ def _same(a, s):
         assert np.array_equal(x, y, equal_nan=x.dtype.kind == "f"), k
 
 
-@pytest.mark.parametrize("edges", [[5.9, 6.1, 5.9], [6.1, 0.5, 12.0], [12.0], [0.5]])
+@pytest.mark.parametrize("edges", [[3.1, 3.4, 3.1], [3.4, 0.5, 12.0], [12.0], [0.5]])   # (the line: 3.26)
 def test_search_equals_scan(edges):
     from paper_2603_15780_amd import sg
     X, F = M.canonical(*M.icosphere(4))

@@ -345,10 +345,10 @@ int sg_backward_workspace_size(sg_mesh mesh, int32_t mode, int64_t n, int32_t wa
  * (synchronous).  A grid takes 4 bytes per cell and 4 per entry of a cell's
  * list: on a smooth mesh some 12 entries per face and no more cells than 128 per
  * face, in cells of 0.65 mean edges; wider cells where faces would fill more than
- * 64 each, or where there is no memory.  Steps that leave a surface of a mesh's
- * size by more than 0.4 mean edges (longer than 0.63 times the root of its largest
- * extent times its mean edge; the least of the handle's meshes) have a grid of
- * their own, in cells of 1.5 edges, built by the first call that makes them.
+ * 64 each, or where there is no memory.  Rays whose steps s |v_t| leave a surface
+ * of the mesh's size by more than 0.8 mean edges (longer than 0.89 times the root of
+ * its largest extent times its mean edge) take a second grid in cells of 1.5 edges,
+ * which the first call with s above 0.02 builds, with a copy of the first.
  * A grid search of 65,536 rays and more on 65,536 faces and more takes a
  * stream-ordered allocation of 8 bytes per ray, in which it orders them; without
  * memory for it, and while a graph is recorded, it takes them as they come.

@@ -55,9 +55,10 @@ struct sg_mesh_s {
     sg::PackedMesh host;   // face order, mesh offsets and edge count
     void* d_pos = nullptr;   // sg_mesh_update_vertices: the new positions before they are accepted (kept)
     // projection-integration Exp: per-face data in user order and one grid per
-    // mesh, in fine cells for short steps and coarse ones for long steps, each built
-    // on the first call that needs it (and again after a vertex update)
+    // mesh, or two for calls that may make long steps, built on the first call that
+    // needs them (and again after a vertex update)
     struct PiCells {
+        int32_t sets = 1;
         sg::PiGrid* grid = nullptr;
         uint32_t* start = nullptr;
         int32_t* face = nullptr;
@@ -67,12 +68,11 @@ struct sg_mesh_s {
     sg::PiFace* d_piface = nullptr;
     PiCells pi_cells[2];
     std::vector<double> pi_ext;   // the meshes' extents
-    double pi_long = 0.0;         // steps longer than this take the coarse cells
     int32_t pi_slim = 0;          // some face is slim
     double pi_tie = 0.0, pi_slack = 0.0;
     sg::PiMesh pi(int cells) const {
         const PiCells& c = pi_cells[cells];
-        return sg::PiMesh{d_piface, c.grid, c.start, c.face, n_faces, n_meshes, pi_slim, pi_tie, pi_slack};
+        return sg::PiMesh{d_piface, c.grid, c.start, c.face, n_faces, n_meshes, pi_slim, c.sets, pi_tie, pi_slack};
     }
     sg::DevMesh dev(int32_t boundary_mode = SG_BOUNDARY_STOP) const {
         const int32_t hole_avoid = boundary_mode == SG_BOUNDARY_AVOID ? park_wait : 0;
@@ -316,6 +316,11 @@ size_t exp_workspace_bytes(const sg_opts& o, int64_t n, int32_t K) {
                                              : sg::exp_persistent_workspace(n, K);
 }
 
+// A step s |v| on a surface of radius R ends (s |v|)^2 / 2 R away from it: from
+// kPiLongStep mean edges of that on, with half a mesh's largest extent for R, a ray
+// takes the grid of wider cells.
+constexpr double kPiLongStep = 0.8;
+
 // One uniform grid per mesh from its extents, in cells of `edges` mean edges
 // (wider if a mesh would need more than cell_cap cells per face).  Returns the
 // number of cells, and the largest absolute coordinate (at least 1) in scale.
@@ -342,7 +347,9 @@ uint64_t pi_grids(const std::vector<int64_t>& fo, const std::vector<double>& ext
             for (int c = 0; c < 3; ++c) mn[c] = mx[c] = 0.0;
             el = 3.0;
         }
-        double h = edges * el / (3.0 * (double)std::max<int64_t>(fm, 1));
+        const double edge = el / (3.0 * (double)std::max<int64_t>(fm, 1));
+        G.far = (float)std::sqrt(kPiLongStep * edge * std::max(mx[0] - mn[0], std::max(mx[1] - mn[1], mx[2] - mn[2])));
+        double h = edges * edge;
         if (!(h > 0.0)) h = 1.0;
         const double cap = (double)std::max<int64_t>(cell_cap * fm, 4096);
         int32_t n[3];
@@ -373,22 +380,21 @@ uint64_t pi_grids(const std::vector<int64_t>& fo, const std::vector<double>& ext
 // The projection-integration data of a handle, built on the device: per-face
 // records in user order and, per mesh, uniform grids whose cells list the faces
 // whose bounding boxes, widened by a margin, meet them.
-// Short steps take cells of 0.65 mean edges: a smooth mesh's query then tests 6
-// faces instead of 11 with one edge and 18 with 1.5 (131,072 rays on 327,680 faces:
-// 1.52, 2.11 and 3.65 ms).  A mesh whose faces differ so much in size that they meet
-// kPiEntries cells each gets wider ones, up to 1.5 edges.  Long steps leave the
-// surface by many cells, and a query d away from it looks through some (2 d / cell)^3:
-// they take cells of 1.5 edges.  A step s on a surface of radius R ends s^2 / 2 R
-// away, and the line lies at kPiLongStep edges of that, with half a mesh's largest
-// extent for R (the smallest step of a handle's meshes).  ms with cells of 0.65 and
-// 1.5 edges and s^2 / 2 R in edges, 20,000 rays on spheres: 20,480 faces 0.16 1.3 and
-// 2.2, 0.28 2.6 and 2.0, 0.43 5.4 and 2.1, 1.1 21 and 9; 81,920 0.31 1.7 and 2.5,
-// 0.55 3.9 and 2.3; 327,680 0.43 1.6 and 2.2, 0.62 1.5 and 2.5, 1.1 3.2 and 2.4, 2.5
-// 12 and 5.0; 1,310,720 0.31 0.29 and 0.32, 0.55 0.82 and 0.30; in steps of the
-// radius, on 20,480 faces, 1,892 and 260.
+// Rays of short steps take cells of 0.65 mean edges: a smooth mesh's query then
+// tests 6 faces instead of 11 with one edge and 18 with 1.5 (131,072 rays on 327,680
+// faces: 1.52, 2.11 and 3.65 ms).  A mesh whose faces differ so much in size that
+// they meet kPiEntries cells each gets wider ones, up to 1.5 edges.  Long steps leave
+// the surface by many cells, and a query d away from it looks through some
+// (2 d / cell)^3: such rays take cells of 1.5 edges (kPiLongStep).  ms with cells of
+// 0.65 and 1.5 edges, 20,000 rays of length up to 1 to 2 on spheres of radius 1, by
+// the longest step's distance in edges: 20,480 faces 0.6 1.3 and 2.2, 1.1 2.6 and 2.0,
+// 1.7 5.4 and 2.1, 4.4 21 and 9; 81,920 0.7 1.7 and 2.5, 1.2 3.9 and 2.3; 327,680 0.6
+// 1.5 and 2.5, 1.1 3.2 and 2.4, 2.5 12 and 5.0; with steps of up to three radii, on
+// 20,480 faces, 1,892 and 260.  Calls of steps below kPiBothSteps |v| build the fine
+// grids alone: their steps are long on rays of many mesh sizes only.
 // Called with pi_mu held; on failure the caller frees what was allocated.
 constexpr uint64_t kPiEntries = 64;   // (a smooth mesh: 12)
-constexpr double kPiLongStep = 0.4;
+constexpr double kPiBothSteps = 0.02;
 
 int build_pi_faces(sg_mesh m) {
     const std::vector<int64_t>& fo = m->host.face_off;
@@ -408,41 +414,32 @@ int build_pi_faces(sg_mesh m) {
     if (e == hipSuccess) e = hipMemcpy(ext.data(), d_ext, ext.size() * sizeof(double), hipMemcpyDeviceToHost);
     (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "projection grid");
-    m->pi_long = INFINITY;
-    for (int k = 0; k < nm; ++k) {
-        if (fo[k + 1] == fo[k]) continue;
-        double size = 0.0, el = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            double mn = INFINITY, mx = -INFINITY;
-            for (int p = 0; p < sg::kPiParts; ++p) {
-                const double* v = &ext[((size_t)k * sg::kPiParts + p) * sg::kPiExtent];
-                mn = std::min(mn, v[c]);
-                mx = std::max(mx, v[3 + c]);
-                if (c == 0) el += v[6];
-            }
-            size = std::max(size, mx - mn);
-        }
-        m->pi_long = std::min(m->pi_long, std::sqrt(kPiLongStep * size * el / (3.0 * (double)(fo[k + 1] - fo[k]))));
-    }
     std::memcpy(&m->pi_slim, &ext.back(), sizeof m->pi_slim);
     m->pi_ext = std::move(ext);
     return SG_OK;
 }
 
-int build_pi_cells(sg_mesh m, int set) {
+int build_pi_cells(sg_mesh m, int both) {
     const std::vector<int64_t>& fo = m->host.face_off;
-    std::vector<sg::PiGrid> grid(fo.size() - 1);
-    sg_mesh_s::PiCells& c = m->pi_cells[set];
-    const size_t grid_bytes = grid.size() * sizeof(sg::PiGrid), sum_at = (grid_bytes + 255) & ~(size_t)255;
+    const size_t nm = fo.size() - 1, sum_at = ((1 + (size_t)both) * nm * sizeof(sg::PiGrid) + 255) & ~(size_t)255;
+    std::vector<sg::PiGrid> grid(nm), wide(nm);
+    sg_mesh_s::PiCells& c = m->pi_cells[both];
     hipError_t e = hipMalloc((void**)&c.grid, sum_at + 16);
     if (e != hipSuccess) return no_memory(e, "projection grid", sum_at + 16);
     auto* sum = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(c.grid) + sum_at);
     uint64_t total = 0, entries[2] = {0, 0};   // cells; cell entries, and the faces that have very many
     double pad = 0.0;
+    auto count = [&] {
+        e = hipMemcpy(c.grid, grid.data(), grid.size() * sizeof(sg::PiGrid), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(both), sum, pad, nullptr);
+        if (e == hipSuccess) e = hipMemcpy(entries, sum, sizeof entries, hipMemcpyDeviceToHost);
+        return e == hipSuccess;
+    };
     for (const double edges : {0.65, 1.0, 1.5}) {
         const bool last = edges == 1.5;
-        if (set == 1 && !last) continue;
         double scale;
+        c.sets = 1;
+        grid.resize(nm);
         total = pi_grids(fo, m->pi_ext, edges, edges < 1.0 ? 128 : 32, grid, scale);
         if (total >= ((uint64_t)1 << 31)) continue;
         // distances within 1e-12 of the largest coordinate are one nearest point (float64 rounding);
@@ -450,12 +447,25 @@ int build_pi_cells(sg_mesh m, int set) {
         m->pi_tie = 1e-12 * scale;
         m->pi_slack = 1e-9 * scale;
         pad = scale * std::ldexp(1.0, -20);
-        e = hipMemcpy(c.grid, grid.data(), grid_bytes, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = sg::launch_pi_entries(m->pi(set), sum, pad, nullptr);
-        if (e == hipSuccess) e = hipMemcpy(entries, sum, sizeof entries, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "projection grid");
+        const bool one = !both || last;
+        if (one)
+            for (sg::PiGrid& G : grid) G.far = INFINITY;
+        if (!count()) return hip_fail(e, "projection grid");
         if (!last && entries[0] > kPiEntries * (uint64_t)m->n_faces) continue;
         if (entries[0] >= ((uint64_t)1 << 32) - 1) break;
+        if (!one) {
+            const uint64_t more = pi_grids(fo, m->pi_ext, 1.5, 32, wide, scale);
+            if (total + more < ((uint64_t)1 << 31)) {
+                for (sg::PiGrid& G : wide) G.cell0 += (uint32_t)total;
+                grid.insert(grid.end(), wide.begin(), wide.end());
+                total += more;
+                c.sets = 2;
+            } else {
+                for (sg::PiGrid& G : grid) G.far = INFINITY;
+            }
+            if (!count()) return hip_fail(e, "projection grid");
+        }
+        if (entries[0] >= ((uint64_t)1 << 32) - 1) continue;
         const size_t bytes = (total + 3 + (uint64_t)sg::scan_tiles((int64_t)total + 1) + entries[1]) * sizeof(uint32_t);
         e = hipMalloc((void**)&c.start, bytes);
         if (e == hipSuccess) e = hipMalloc((void**)&c.face, std::max<uint64_t>(entries[0], 1) * sizeof(int32_t));
@@ -468,21 +478,20 @@ int build_pi_cells(sg_mesh m, int set) {
     if (!c.start) return fail(SG_E_OOM, "projection grid too large");
     const int64_t n_large = (int64_t)entries[1];
     uint32_t *cells = c.start + 1, *large = cells + total + 1, *tile = large + 1 + n_large;
-    e = sg::launch_pi_count(m->pi(set), cells, (int64_t)total, pad, tile, large, n_large, nullptr);
-    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(set), cells, c.face, pad, large, n_large, nullptr);
+    e = sg::launch_pi_count(m->pi(both), cells, (int64_t)total, pad, tile, large, n_large, nullptr);
+    if (e == hipSuccess) e = sg::launch_pi_fill(m->pi(both), cells, c.face, pad, large, n_large, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // later calls read it on any stream
     if (e != hipSuccess) return hip_fail(e, "projection grid");
     return SG_OK;
 }
 
-// out: the handle's data with the cells for steps of this length.  Where these are
-// not built yet and cannot be now (a graph is recorded on the stream, or there is no
-// memory), the other cells do: they give the same results.
+// out: the handle's data with the grids for calls of this step.  Where these are not
+// built yet and cannot be now (a graph is recorded on the stream, or there is no
+// memory), the ones that are do: the results are the same.
 int ensure_pi(sg_mesh m, double step, hipStream_t st, sg::PiMesh& out) {
     std::lock_guard<std::mutex> lock(m->pi_mu);
-    auto cells = [&] { return step > m->pi_long ? 1 : 0; };
-    int use = cells();
-    if (m->pi_ext.empty() || !m->pi_cells[use].ready) {
+    int use = step > kPiBothSteps ? 1 : 0;
+    if (!m->pi_cells[use].ready) {
         const bool other = m->pi_cells[1 - use].ready;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (other && hipStreamIsCapturing(st, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) {
@@ -494,7 +503,6 @@ int ensure_pi(sg_mesh m, double step, hipStream_t st, sg::PiMesh& out) {
         int rc = SG_OK;
         try {
             if (m->pi_ext.empty()) rc = build_pi_faces(m);
-            use = cells();
             if (rc == SG_OK) rc = build_pi_cells(m, use);
         } catch (const std::bad_alloc&) {
             rc = fail(SG_E_OOM, "out of host memory");

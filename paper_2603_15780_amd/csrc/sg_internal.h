@@ -108,16 +108,18 @@ struct PiGrid {
     int32_t nx, ny, nz;       // cells per axis
     uint32_t cell0;           // first cell of this mesh in the handle's cell arrays
     int32_t face0, face1;     // the mesh's user face range [face0, face1)
+    float far;                // rays of longer steps take the mesh's other grid (PiMesh::sets)
 };
 
 struct PiMesh {
     const PiFace* face;        // [n_faces] in user order
-    const PiGrid* grid;        // [n_meshes]
+    const PiGrid* grid;        // [sets * n_meshes]: each mesh's grid, then each mesh's in wider cells
     const uint32_t* cell_start;// [total cells + 1] offsets into cell_face
     const int32_t* cell_face;  // user face ids
     int64_t n_faces;
     int32_t n_meshes;
     int32_t slim;              // some face is PiFace::slim
+    int32_t sets;              // 1, or 2 with the grids of wider cells
     double tie;                // distances within tie of the smallest are a tie (a shared nearest point)
     double slack;              // extra reach of the cell search over the tie (rounding of box distances)
 };

@@ -503,7 +503,8 @@ __global__ __launch_bounds__(kPiBlock) void k_pi_exp_grid(PiMesh P, PiArgsT<T> a
         pi_write_bad(a, i);
         return;
     }
-    const PiGrid G = P.grid[r.mesh];
+    const bool far = a.step * r.L > (double)P.grid[r.mesh].far;
+    const PiGrid G = P.grid[far ? r.mesh + P.n_meshes : r.mesh];
     int32_t status = kRayOk;
     while (r.l < r.L) {
         if (r.steps >= a.max_steps) {
@@ -689,8 +690,8 @@ __device__ __forceinline__ unsigned long long box_cells(const int (&i0)[3], cons
 constexpr unsigned long long kPiLane = 512;
 
 template <class Add>
-__device__ __forceinline__ bool face_cells(const PiMesh& P, int64_t u, double pad, Add&& add) {
-    const PiGrid G = P.grid[mesh_of(P, (int32_t)u)];
+__device__ __forceinline__ bool face_cells(const PiMesh& P, int64_t u, int set, double pad, Add&& add) {
+    const PiGrid G = P.grid[set * P.n_meshes + mesh_of(P, (int32_t)u)];
     int i0[3], i1[3];
     face_box(P, G, u, pad, i0, i1);
     if (box_cells(i0, i1) > kPiLane) return false;
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(256) void k_pi_entries(PiMesh P, unsigned long long
     unsigned long long n = 0ull;
     if (u < P.n_faces) {
         int i0[3], i1[3];
-        face_box(P, P.grid[mesh_of(P, (int32_t)u)], u, pad, i0, i1);
+        face_box(P, P.grid[(int)blockIdx.y * P.n_meshes + mesh_of(P, (int32_t)u)], u, pad, i0, i1);
         n = box_cells(i0, i1);
     }
     if (n > kPiLane) atomicAdd(sum + 1, 1ull);
@@ -719,17 +720,18 @@ __global__ __launch_bounds__(256) void k_pi_entries(PiMesh P, unsigned long long
     if ((threadIdx.x & 63u) == 0u) atomicAdd(sum, n);
 }
 
-// large: the number of faces left to k_pi_large, then these
+// large: the number of faces left to k_pi_large, then these (the set of grids in the top bit)
 __global__ __launch_bounds__(256) void k_pi_count(PiMesh P, uint32_t* cells, double pad, uint32_t* large) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < P.n_faces && !face_cells(P, u, pad, [&](uint32_t c) { atomicAdd(cells + c, 1u); }))
-        large[1u + atomicAdd(large, 1u)] = (uint32_t)u;
+    const int set = (int)blockIdx.y;
+    if (u < P.n_faces && !face_cells(P, u, set, pad, [&](uint32_t c) { atomicAdd(cells + c, 1u); }))
+        large[1u + atomicAdd(large, 1u)] = (uint32_t)u | ((uint32_t)set << 31);
 }
 
 __global__ __launch_bounds__(256) void k_pi_fill(PiMesh P, uint32_t* cells, int32_t* cell_face, double pad) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (u < P.n_faces)
-        (void)face_cells(P, u, pad, [&](uint32_t c) { cell_face[atomicAdd(cells + c, 1u)] = (int32_t)u; });
+        (void)face_cells(P, u, (int)blockIdx.y, pad, [&](uint32_t c) { cell_face[atomicAdd(cells + c, 1u)] = (int32_t)u; });
 }
 
 // The large faces, a row of blocks each.
@@ -738,8 +740,9 @@ __global__ __launch_bounds__(256) void k_pi_large(PiMesh P, const uint32_t* larg
                                                   double pad) {
     const uint32_t n_large = large[0];
     for (uint32_t k = blockIdx.y; k < n_large; k += gridDim.y) {
-        const int32_t u = (int32_t)large[1u + k];
-        const PiGrid G = P.grid[mesh_of(P, u)];
+        const uint32_t e = large[1u + k];
+        const int32_t u = (int32_t)(e & 0x7fffffffu);
+        const PiGrid G = P.grid[(int)(e >> 31) * P.n_meshes + mesh_of(P, u)];
         int i0[3], i1[3];
         face_box(P, G, u, pad, i0, i1);
         const uint32_t nx = (uint32_t)(i1[0] - i0[0] + 1), ny = (uint32_t)(i1[1] - i0[1] + 1), n = nx * ny * (uint32_t)(i1[2] - i0[2] + 1);
@@ -1016,7 +1019,7 @@ hipError_t launch_pi_faces(const DevMesh& M, PiFace* face, uint32_t* slim, hipSt
 
 hipError_t launch_pi_entries(const PiMesh& P, unsigned long long* sum, double pad, hipStream_t s) {
     hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(sum), (int64_t)4);
-    hipLaunchKernelGGL(k_pi_entries, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, sum, pad);
+    hipLaunchKernelGGL(k_pi_entries, dim3((unsigned)((P.n_faces + 255) / 256), (unsigned)P.sets), dim3(256), 0, s, P, sum, pad);
     return hipGetLastError();
 }
 
@@ -1033,7 +1036,8 @@ hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, doub
     hipLaunchKernelGGL(k_pi_zero, dim3((unsigned)std::min<int64_t>((total + 256) / 256, 8192)), dim3(256), 0, s, cells - 1,
                        total + 2);
     hipLaunchKernelGGL(k_pi_zero, dim3(1), dim3(256), 0, s, large, (int64_t)1);
-    hipLaunchKernelGGL(k_pi_count, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, cells, pad, large);
+    hipLaunchKernelGGL(k_pi_count, dim3((unsigned)((P.n_faces + 255) / 256), (unsigned)P.sets), dim3(256), 0, s, P, cells, pad,
+                       large);
     large_faces(P, n_large, large, cells, nullptr, pad, s);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? launch_scan(cells, total + 1, tile, s) : e;
@@ -1041,7 +1045,8 @@ hipError_t launch_pi_count(const PiMesh& P, uint32_t* cells, int64_t total, doub
 
 hipError_t launch_pi_fill(const PiMesh& P, uint32_t* cells, int32_t* cell_face, double pad, const uint32_t* large,
                           int64_t n_large, hipStream_t s) {
-    hipLaunchKernelGGL(k_pi_fill, dim3((unsigned)((P.n_faces + 255) / 256)), dim3(256), 0, s, P, cells, cell_face, pad);
+    hipLaunchKernelGGL(k_pi_fill, dim3((unsigned)((P.n_faces + 255) / 256), (unsigned)P.sets), dim3(256), 0, s, P, cells, cell_face,
+                       pad);
     large_faces(P, n_large, large, cells, cell_face, pad, s);
     return hipGetLastError();
 }

@@ -1,5 +1,6 @@
-"""Steps that leave the surface by many cells take a grid of wider cells: the same result as the scan on both
-sides of the line, in any order of calls on a handle, and no slower than short cells."""
+"""Rays whose steps leave the surface by many cells take a grid of wider cells: the same
+result as the scan on both sides of the line, in any order of calls on a handle, and no
+slower than short cells."""
 import time
 
 import numpy as np
@@ -25,13 +26,14 @@ def _same(a, s):
         assert np.array_equal(x, y, equal_nan=x.dtype.kind == "f"), k
 
 
-@pytest.mark.parametrize("edges", [[3.1, 3.4, 3.1], [3.4, 0.5, 12.0], [12.0], [0.5]])   # (the line: 3.26)
-def test_search_equals_scan(edges):
+# (on these 5,120 faces rays of steps longer than 0.35 take the wide cells; lengths to 2)
+@pytest.mark.parametrize("steps", [[0.3, 0.01, 0.3], [0.01, 0.3, 0.01], [0.15], [0.9], [0.02, 0.03]])
+def test_search_equals_scan(steps):
     from paper_2603_15780_amd import sg
     X, F = M.canonical(*M.icosphere(4))
     t, mesh = _rays(X, F, 1025, 2.0), sg.Mesh(X, F)
-    for k, e in enumerate(edges):
-        kw = dict(step=e * mesh.info()["mean_edge"], want_steps=True)
+    for k, step in enumerate(steps):
+        kw = dict(step=step, want_steps=True)
         _same(mesh.pi_exp(*t, **kw), mesh.pi_exp(*t, search=sg.PI_SCAN, **kw))
         if k == 0:   # both grids are for the positions of the moment
             X = (X * (1.0 + 0.05 * np.sin(3.0 * X[:, [1, 2, 0]]))).astype(np.float32)
@@ -39,20 +41,33 @@ def test_search_equals_scan(edges):
             t = _rays(X, F, 1025, 2.0)
 
 
+def test_several_meshes():
+    """Each mesh of a handle has its own line: here the large one's rays are short of it."""
+    from paper_2603_15780_amd import sg
+    parts = [M.canonical(*M.icosphere(3)), M.canonical(*M.torus_grid(60, 20, 0.2, np.random.default_rng(2)))]
+    parts[0] = (8.0 * parts[0][0], parts[0][1])
+    X, F = np.concatenate([p[0] for p in parts]).astype(np.float32), np.concatenate([p[1] for p in parts])
+    vo, fo = (np.cumsum([0] + [p[k].shape[0] for p in parts]) for k in (0, 1))
+    Fg = np.concatenate([p[1] + o for p, o in zip(parts, vo)]).astype(np.int32)
+    mesh, t = sg.Mesh(X, F, vert_offsets=vo, face_offsets=fo), _rays(X, Fg, 1025, 2.0)
+    for step in (0.01, 0.4):
+        kw = dict(step=step, want_steps=True)
+        _same(mesh.pi_exp(*t, **kw), mesh.pi_exp(*t, search=sg.PI_SCAN, **kw))
+
+
 def test_backward_over_both_grids():
     from paper_2603_15780_amd import sg
     X, F = M.canonical(*M.icosphere(4))
     (f, b, v, _), h = _rays(X, F, 257, 1.0), sg.Mesh(X, F)
     g = torch.from_numpy(np.random.default_rng(4).normal(size=(257, 3)).astype(np.float32)).cuda()
-    for e in (1.0, 12.0):
-        step = e * h.info()["mean_edge"]
+    for step in (0.01, 0.8):
         for x, y in zip(h.pi_backward(sg.BWD_GFD, f, b, v, g, step=step),
                         h.pi_backward(sg.BWD_GFD, f, b, v, g, step=step, search=sg.PI_SCAN)):
             assert torch.equal(x, y)
 
 
 def test_long_steps_cost_no_more_than_wide_cells():
-    """Steps of the mesh's radius on 20,480 faces: cells of 0.65 edges took 1.9 s for
+    """Steps of up to three radii on 20,480 faces: cells of 0.65 edges took 1.9 s for
     2,048 rays, cells of 1.5 edges take 0.26 (0.6 before the search had one visit)."""
     from paper_2603_15780_amd import sg
     X, F = M.canonical(*M.icosphere(5))
@@ -71,10 +86,10 @@ def test_a_step_not_met_before_in_a_graph():
     from paper_2603_15780_amd import sg
     X, F = M.canonical(*M.icosphere(4))
     mesh, t = sg.Mesh(X, F), _rays(X, F, 500, 2.0)
-    step = 8.0 * mesh.info()["mean_edge"]
+    step = 0.6
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
-        mesh.pi_exp(*t, step=0.5 * mesh.info()["mean_edge"])
+        mesh.pi_exp(*t, step=0.01)
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=s):

@@ -244,7 +244,7 @@ def test_wait_of_an_odd_step(lib, kind, wait):
 
 @pytest.mark.parametrize("first,then", [(0.01, 0.5), (0.5, 0.01)])
 def test_projection_with_the_other_cells(lib, first, then):
-    """Short and long steps (from 0.09 on here) have grids of their own.  A call whose
+    """Calls of short and of long steps (from 0.02 on) have grids of their own.  A call whose
     grid is not built yet takes the other's where it cannot build it: while a graph is
     recorded, and without memory."""
     h, cells = lib.mesh(*_canonical("icosphere")), []

@@ -247,8 +247,8 @@ __device__ __forceinline__ double face_dist2(D3 x0, D3 x1, D3 x2, D3 q) {
 // -1 when more than kPiCand faces tie and the search has to be the general one.
 // Where the cell of q does not settle it, the rings of cells around it follow
 // (grid_cells): with the general search there instead, 131,072 rays on 327,680
-// faces in steps of 0.1 (ten edges) took 19.6 ms, now 5.0, and on a rough mesh
-// of 81,920 faces in steps of 0.03 35.8, now 10.4.
+// faces in steps of 0.1 |v| took 19.6 ms, now 5.6, and on a rough mesh of 81,920
+// faces in steps of 0.03 35.8, now 13.4.
 constexpr int kPiCand = 8;
 constexpr int kPiAhead = 4;   // 1,000 rays on 327,680 faces: 1.63 ms with one record in flight, 1.01 with four
 constexpr int kPiBlock = 256;
